@@ -85,6 +85,12 @@ LatticeDev make_latdev(int Lx, int Ly) {
 // Register-layout sequence covering local transform bits [x0, x1) with
 // windows of g.R bits from the top; g.full = number of layouts when every
 // window is complete and a straight-line kernel exists for it.
+// Register windows of a one-group plan (observables and adjoint; the ramp
+// itself runs in the one-workgroup kernel, which has a layout of its own).
+static bool full_resident_ok(int R, int NL) {
+    return (R == 2 && NL == 4) || (R == 4 && NL == 2) || (R == 4 && NL == 3) || (R == 3 && NL == 4);
+}
+
 static void plan_layouts(GroupGeom &g, bool resident) {
     const int R = g.R;
     const int width = g.x1 - g.x0;
@@ -1056,12 +1062,10 @@ z2h_status run_levels(const Plan &P, void *states, const JobSet &J, hipStream_t 
         a.states = states;
         a.jobs = J.d_jobs;
         a.job_inline = J.inl;
-        a.geom = P.geom[0];
         a.lat = P.lat;
-        a.job0 = 0;
         hipEvent_t e0, e1;
         timed_begin(s, e0, e1);
-        hipError_t e = launch_resident(P.c128, a.geom.R, a, (unsigned)J.njobs, lds_bytes(P, a.geom, a.geom.R), s);
+        hipError_t e = P.geom[0].full ? launch_resident(P.c128, a, (unsigned)J.njobs, s) : hipErrorInvalidValue;
         if (e != hipSuccess) return fail(Z2H_ERR_HIP, "resident kernel launch failed: %s", hipGetErrorString(e));
         timed_end(s, e0, e1, 3);
         return Z2H_OK;

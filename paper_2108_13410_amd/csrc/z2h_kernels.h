@@ -51,10 +51,7 @@ struct TablesArgs {
 struct ResidentArgs {
     void *states;
     const JobDev *jobs;
-    GroupGeom geom;            // whole state as one tile
     LatticeDev lat;
-    int32_t job0;              // first job of this launch
-    int32_t pad;
     JobDev job_inline;         // used when jobs is null (single state)
 };
 
@@ -135,8 +132,7 @@ bool adj_shape_ok(int R, int NL);
 
 hipError_t launch_level(bool c128, int R, const LevelArgs &a, unsigned nblocks, size_t lds,
                         hipStream_t s);
-hipError_t launch_resident(bool c128, int R, const ResidentArgs &a, unsigned njobs, size_t lds,
-                           hipStream_t s);
+hipError_t launch_resident(bool c128, const ResidentArgs &a, unsigned njobs, hipStream_t s);
 hipError_t launch_obs(bool c128, int R, const ObsArgs &a, unsigned workers, unsigned njobs,
                       size_t lds, hipStream_t s);
 hipError_t launch_obs_finalize(const FinalArgs &a, unsigned njobs, hipStream_t s);
@@ -151,9 +147,10 @@ LevelOp level_op_host(int lev, int K, int S, int k0, int order);
 bool full_level_ok(int R, int NL);
 bool pair_level_ok(bool c128, int R, int NL);  // two-tile blocks compiled for this shape
 bool cx_level_ok(int R, int NL);               // component-exchange kernels compiled for this shape
-bool full_resident_ok(int R, int NL);
 
 // Set the dynamic-LDS limit of every kernel (call before graph capture).
 hipError_t prepare_kernels();
+hipError_t prepare_resident();
+hipError_t set_lds(const void *fn, size_t lds);  // of one kernel, to the largest block any plan uses
 
 }  // namespace z2h

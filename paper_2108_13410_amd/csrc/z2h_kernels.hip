@@ -21,6 +21,7 @@
 
 #include "z2h_internal.h"
 #include "z2h_kernels.h"
+#include "z2h_sched.h"
 #include "z2h_tile.h"
 
 namespace z2h {
@@ -106,146 +107,6 @@ __device__ __forceinline__ void apply_phase(Cx<Real> (&v)[1 << R], const LayCtx<
         // pressure when a block holds two tiles)
         if (PHASE_CHUNK && (idx & (PHASE_CHUNK - 1)) == PHASE_CHUNK - 1) __builtin_amdgcn_sched_barrier(0);
     }
-}
-
-// Sum of |v_q|^2 over a thread's register elements: pairwise in the storage
-// precision (complex64 steps accumulate in FP32), returned as FP64 for the
-// block and grid reductions.
-template <typename Real, int R>
-__device__ __forceinline__ double sumsq(const Cx<Real> (&v)[1 << R]) {
-    Real a[1 << R];
-#pragma unroll
-    for (int q = 0; q < (1 << R); ++q) a[q] = v[q].x * v[q].x + v[q].y * v[q].y;
-#pragma unroll
-    for (int h = (1 << R) >> 1; h > 0; h >>= 1) {
-#pragma unroll
-        for (int q = 0; q < h; ++q) a[q] += a[q + h];
-    }
-    return (double)a[0];
-}
-
-
-// Norm partials and traces live in global memory; accessing them through
-// global-address-space pointers keeps them off the LDS counter (generic
-// "flat" accesses count on both, and would make LDS waits wait for them).
-typedef __attribute__((address_space(1))) double *GlobalDoubles;
-__device__ __forceinline__ double gld(const double *p, int64_t i) { return ((GlobalDoubles)p)[i]; }
-__device__ __forceinline__ void gst(double *p, int64_t i, double v) { ((GlobalDoubles)p)[i] = v; }
-
-// Job records are read-only during a launch: read them through the constant
-// address space so that the (block-uniform) record is fetched with scalar
-// loads, whose completion does not wait on the block's outstanding tile loads.
-typedef const __attribute__((address_space(4))) uint32_t *ConstWords;
-static_assert(sizeof(JobDev) % 4 == 0, "job record is copied in 32-bit words");
-
-__device__ __forceinline__ JobDev job_record(const JobDev *jobs, int jb, const JobDev &inl) {
-    if (!jobs) return inl;
-    JobDev J;
-    uint32_t *d = reinterpret_cast<uint32_t *>(&J);
-    const ConstWords src = (ConstWords)(jobs + jb);
-#pragma unroll
-    for (int i = 0; i < (int)(sizeof(JobDev) / 4); ++i) d[i] = src[i];
-    return J;
-}
-
-// Job of a packed launch's block-job b (index list read through the constant
-// address space: a scalar load).
-__device__ __forceinline__ int job_index(const int32_t *jidx, int b) {
-    typedef const __attribute__((address_space(4))) int32_t *ConstInts;
-    return ((ConstInts)jidx)[b];
-}
-
-// ---------------------------------------------------------------- schedule
-
-__device__ __forceinline__ double sched_s(const JobDev &J, int k, int zkind) {
-#pragma clang fp contract(off)
-    typedef const __attribute__((address_space(4))) double *ConstDoubles;
-    const double *arr = zkind ? J.sZ : J.sX;
-    if (arr) return ((ConstDoubles)arr)[k];  // read-only; scalar load
-    return J.sampling ? (double)(k + 1) / (double)J.M : ((double)k + 0.5) / (double)J.M;
-}
-
-// (coupling, field) of the given basis at step k: inner (Z) basis uses
-// (JB, hz) at sZ, outer (X) basis uses (JA, hx) at sX.
-__device__ __forceinline__ void coup(const JobDev &J, int basis, int k, double &Jc, double &h) {
-#pragma clang fp contract(off)
-    const double s = sched_s(J, k, basis == 0);
-    const int ij = basis == 0 ? 1 : 0, ih = basis == 0 ? 3 : 2;
-    Jc = (1.0 - s) * J.c0[ij] + s * J.c1[ij];
-    h = (1.0 - s) * J.c0[ih] + s * J.c1[ih];
-}
-
-// Angles of a phase pass: full step ka (duration dt) or half steps ka, kb.
-__device__ __forceinline__ void phase_angles(const JobDev &J, const LevelOp &op, double &alpha,
-                                             double &beta) {
-#pragma clang fp contract(off)
-    double Ja, ha, Jb = 0, hb = 0;
-    coup(J, op.basis, op.ka, Ja, ha);
-    if (op.full) {
-        alpha = J.dt * Ja;
-        beta = J.dt * ha;
-        return;
-    }
-    if (op.kb >= 0) coup(J, op.basis, op.kb, Jb, hb);
-    alpha = 0.5 * J.dt * (Ja + Jb);
-    beta = 0.5 * J.dt * (ha + hb);
-}
-
-// Level sequence of one job (see the host planner for the derivation): the
-// visited group zig-zags between group 0 (computational basis reached) and
-// group K-1 (Hadamard basis reached).
-__host__ __device__ inline LevelOp level_op(int lev, int K, int S, int k0, int order) {
-    LevelOp op{0, kIdle, 0, -1, -1, 0, 0, 0};
-    const int P = 2 * (K - 1);
-    const int nlev = order == 0 ? P * (S + 1) + 1 : P * S + 1;
-    if (S <= 0 || lev < 0 || lev >= nlev) return op;
-    const int r = lev % P;
-    op.group = r <= K - 1 ? r : P - r;
-    const int j = lev / P;
-    if (op.group != 0 && op.group != K - 1) {
-        op.kind = kPlainH;
-        return op;
-    }
-    if (op.group == K - 1 && r == K - 1) {
-        // outer visit j
-        op.basis = 1;
-        if (order == 0) {
-            op.kind = kPhaseB;
-            if (j == 0) {
-                op.ka = k0; op.kb = -1; op.full = 0;
-            } else if (j == S) {
-                op.ka = k0 + S - 1; op.kb = -1; op.full = 0;
-            } else {
-                op.ka = k0 + j - 1; op.kb = k0 + j; op.full = 0;
-            }
-            op.renorm = j >= 1 ? 1 : 0;
-        } else {
-            op.kind = kPhaseB;
-            op.ka = k0 + j; op.full = 1;
-            op.renorm = 1;
-        }
-        return op;
-    }
-    // inner visit j (group 0)
-    op.basis = 0;
-    if (order == 0) {
-        if (j == 0 || j == S + 1) {
-            op.kind = kPlainH;
-        } else {
-            op.kind = kPhaseB;
-            op.ka = k0 + j - 1; op.full = 1;
-            op.norm = 1;
-        }
-    } else {
-        if (j == 0) {
-            op.kind = kHalfIn; op.ka = k0; op.kb = -1; op.full = 0; op.norm = 1;
-        } else if (j == S) {
-            op.kind = kHalfOut; op.ka = k0 + S - 1; op.kb = -1; op.full = 0;
-        } else {
-            op.kind = kPhaseB; op.ka = k0 + j - 1; op.kb = k0 + j; op.full = 0; op.norm = 1;
-        }
-    }
-    return op;
 }
 
 // ---------------------------------------------------------------- level kernel
@@ -791,82 +652,6 @@ hipError_t launch_tables(bool c128, const TablesArgs &a, unsigned nlevels, hipSt
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- resident kernel
-//
-// Whole ramp of a small lattice inside one workgroup: the state never leaves
-// registers between steps.  Same operation order, angles and renormalization
-// rule as the level sequence of the pass kernels.  The whole state is one
-// group of NL * R = n transformed bits.
-
-template <typename Real, int R, int NL>
-__global__ void __launch_bounds__(512) resident_kernel(ResidentArgs a) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    const GroupGeom &g = a.geom;
-    const uint32_t t = threadIdx.x;
-    const JobDev J = job_record(a.jobs, a.job0 + blockIdx.x, a.job_inline);
-    const int S = J.steps, k0 = J.k_begin;
-    if (S <= 0) return;
-    const int n = a.lat.n, nst = a.lat.nst, W = n + 1;
-    const int x1 = g.x1, p0 = x1 - R, pl = x1 - R * NL;
-
-    Cx<Real> *lds = reinterpret_cast<Cx<Real> *>(smem);
-    const uint32_t lds_elems = (1u << g.m) + (1u << (g.m - R));
-    Cx<Real> *tab = lds + lds_elems;
-    double2 *fac = table_scratch(smem);
-    double *red = align16<double>(tab + (nst + 1) * W);
-
-    Cx<Real> v[1 << R];
-    Cx<Real> *st = reinterpret_cast<Cx<Real> *>(a.states) + J.offset;
-    LayCtx<R> L0, Lt;
-    lay_ctx<R>(L0, g, a.lat, 0, p0, t, true);
-    lay_ctx<R>(Lt, g, a.lat, 0, pl, t, true);
-    load_tile<Real, R>(v, st, L0);
-
-    double last_norm = 1.0;
-    const double two_mn = ldexp(1.0, -n);
-
-    // outer (Hadamard-basis) phase: transform, phase, transform back
-    auto outer = [&](const LevelOp &op, bool have_norm) {
-        double alpha, beta;
-        phase_angles(J, op, alpha, beta);
-        double scale = two_mn;
-        if (op.renorm && have_norm) {
-            if (J.renorm) scale *= 1.0 / sqrt(last_norm);
-            if (t == 0 && J.norm_trace) gst(J.norm_trace, op.ka - k0, last_norm);
-        }
-        build_table<Real>(tab, fac, nst, n, alpha, beta, scale);
-        fwd_full<Real, R, NL>(v, lds, x1, t);
-        apply_phase<Real, R>(v, Lt, 1, n, tab);
-        bwd_full<Real, R, NL>(v, lds, x1, t);
-    };
-    // inner (computational-basis) phase, with the norm measured first
-    auto inner = [&](const LevelOp &op) {
-        double alpha, beta;
-        phase_angles(J, op, alpha, beta);
-        if (op.norm) last_norm = block_sum(sumsq<Real, R>(v), red);
-        build_table<Real>(tab, fac, nst, n, alpha, beta, 1.0);
-        apply_phase<Real, R>(v, L0, 0, n, tab);
-    };
-
-    // The level sequence with K = 2 groups, walked in its fixed pattern:
-    // order 0: X(0) [Z(j) X(j+1)] ..., order 1: Z(0) [X(j) Z(j+1)] ...
-    const int P = 2;
-    if (J.order == 0) {
-        outer(level_op(1, 2, S, k0, 0), false);
-        for (int j = 1; j <= S; ++j) {
-            inner(level_op(P * j, 2, S, k0, 0));
-            outer(level_op(P * j + 1, 2, S, k0, 0), true);
-        }
-    } else {
-        inner(level_op(0, 2, S, k0, 1));
-        for (int j = 0; j < S; ++j) {
-            outer(level_op(P * j + 1, 2, S, k0, 1), true);
-            inner(level_op(P * (j + 1), 2, S, k0, 1));
-        }
-    }
-    store_tile<Real, R>(v, st, L0);
-}
-
 // ---------------------------------------------------------------- adjoint
 //
 // Reverse evolution for the gradient of <psi_M|H|psi_M> with respect to the
@@ -1197,7 +982,7 @@ __global__ void reduce_parts_stage2(const JobDev *jobs, JobDev inl, int parts, i
 static std::mutex g_lds_mu;
 static std::set<const void *> g_lds_done;
 
-static hipError_t set_lds(const void *fn, size_t lds) {
+hipError_t set_lds(const void *fn, size_t lds) {
     if (lds <= 65536) return hipSuccess;
     std::lock_guard<std::mutex> lk(g_lds_mu);
     if (g_lds_done.count(fn)) return hipSuccess;
@@ -1300,17 +1085,11 @@ bool pair_level_ok(bool c128, int R, int NL) {
 // (R, NL) shapes compiled as straight-line kernels.
 #define Z2H_FULL_LEVEL_SHAPES(X) \
     X(5, 1) X(5, 2) X(5, 3) X(4, 1) X(4, 2) X(4, 3) X(3, 1) X(3, 2) X(3, 3) X(2, 2) X(2, 3) X(2, 4)
-#define Z2H_FULL_RESIDENT_SHAPES(X) X(2, 4) X(4, 2) X(4, 3) X(3, 4) X(5, 2)
 #define Z2H_ADJ_SHAPES(X) Z2H_FULL_LEVEL_SHAPES(X) X(3, 4)
 
 bool full_level_ok(int R, int NL) {
 #define Z2H_OK_SHAPE(r, nl) if (R == r && NL == nl) return true;
     Z2H_FULL_LEVEL_SHAPES(Z2H_OK_SHAPE)
-    return false;
-}
-
-bool full_resident_ok(int R, int NL) {
-    Z2H_FULL_RESIDENT_SHAPES(Z2H_OK_SHAPE)
 #undef Z2H_OK_SHAPE
     return false;
 }
@@ -1330,26 +1109,6 @@ static hipError_t do_level(const LevelArgs &a, dim3 grid, size_t lds, hipStream_
     if (a.geom.m - R < 6 || a.geom.m - R > 9) return hipErrorInvalidConfiguration;  // launch bounds
     if (a.geom.full) return level_full_dispatch<Real>(a, grid, lds, s);
     return a.nt ? do_level_nt<Real, R, true>(a, grid, lds, s) : do_level_nt<Real, R, false>(a, grid, lds, s);
-}
-
-template <typename Real, int R, int NL>
-static hipError_t do_resident_shape(const ResidentArgs &a, dim3 grid, size_t lds, hipStream_t s) {
-    const void *fn = reinterpret_cast<const void *>(&resident_kernel<Real, R, NL>);
-    hipError_t e = set_lds(fn, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((resident_kernel<Real, R, NL>), grid, dim3(1u << (a.geom.m - R)), lds, s, a);
-    return hipGetLastError();
-}
-
-template <typename Real, int R>
-static hipError_t do_resident(const ResidentArgs &a, dim3 grid, size_t lds, hipStream_t s) {
-    if (a.geom.m - R < 6 || a.geom.m - R > 9) return hipErrorInvalidConfiguration;  // launch bounds
-    const int NL = a.geom.full;
-#define Z2H_CALL_SHAPE(r, nl) \
-    if (R == r && NL == nl) return do_resident_shape<Real, r, nl>(a, grid, lds, s);
-    Z2H_FULL_RESIDENT_SHAPES(Z2H_CALL_SHAPE)
-#undef Z2H_CALL_SHAPE
-    return hipErrorInvalidValue;
 }
 
 template <typename Real, int R>
@@ -1413,10 +1172,6 @@ static hipError_t prep_real() {
     if (e == hipSuccess) e = set_lds(reinterpret_cast<const void *>(&level_kernel_cx<Real, r, nl, kPlainH>), kMaxLdsBytes);
     Z2H_CX_SHAPES(Z2H_PREP_CX)
 #undef Z2H_PREP_CX
-#define Z2H_PREP_RES(r, nl) \
-    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void *>(&resident_kernel<Real, r, nl>), kMaxLdsBytes);
-    Z2H_FULL_RESIDENT_SHAPES(Z2H_PREP_RES)
-#undef Z2H_PREP_RES
     return e;
 }
 
@@ -1429,17 +1184,13 @@ hipError_t prepare_kernels() {
 #undef Z2H_PREP_ADJ
     if (e == hipSuccess) e = prep_real<float>();
     if (e == hipSuccess) e = prep_real<double>();
+    if (e == hipSuccess) e = prepare_resident();
     return e;
 }
 
 hipError_t launch_level(bool c128, int R, const LevelArgs &a, unsigned nblocks, size_t lds,
                         hipStream_t s) {
     Z2H_DISPATCH(do_level, a, dim3(nblocks), lds, s);
-}
-
-hipError_t launch_resident(bool c128, int R, const ResidentArgs &a, unsigned njobs, size_t lds,
-                           hipStream_t s) {
-    Z2H_DISPATCH(do_resident, a, dim3(njobs), lds, s);
 }
 
 hipError_t launch_obs(bool c128, int R, const ObsArgs &a, unsigned workers, unsigned njobs,
