@@ -858,8 +858,10 @@ size_t lds_bytes(const Plan &P, const GroupGeom &g, int R) {
 }
 
 size_t obs_lds_bytes(const Plan &P, const GroupGeom &g, int R) {
+    // the exchange region, which also takes the waves' sums (64 doubles a wave)
     const size_t elems = ((size_t)1 << g.m) + ((size_t)1 << (g.m - R));
-    return ((elems * P.esize + 15) & ~(size_t)15) + 16 * sizeof(double);
+    const size_t rows = (size_t)8 << (g.m - R);
+    return ((std::max(elems * P.esize, rows) + 15) & ~(size_t)15) + 16 * sizeof(double);
 }
 
 
@@ -1221,9 +1223,7 @@ z2h_status run_observe(const Plan &P, const void *states, int njobs, const ObsBu
         a.src_off = gi == 0 ? B.src_off : B.dst_off;
         a.dst = gi == P.K - 1 ? nullptr : B.scratch;
         a.dst_off = B.dst_off;
-        a.redZ = gi == 0;
         a.doH = 1;
-        a.redX = gi == P.K - 1;
         a.part_z = gi == 0 ? B.partZ : nullptr;
         a.part_x = gi == P.K - 1 ? B.partX : nullptr;
         if (gi == 0) wZ = w;

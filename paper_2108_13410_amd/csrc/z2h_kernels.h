@@ -64,10 +64,10 @@ struct ObsArgs {
     LatticeDev lat;
     uint32_t zloops[kMaxLoops], xloops[kMaxLoops];
     int32_t nz, nx;
-    int32_t redZ, doH, redX;
+    int32_t doH;
     int32_t pad;
-    double *part_z;            // per-workgroup records of computational-basis sums (or null)
-    double *part_x;            // per-workgroup records of Hadamard-basis sums (or null)
+    double *part_z;            // per-workgroup records of computational-basis sums (or null: not reduced)
+    double *part_x;            // per-workgroup records of Hadamard-basis sums (or null: not reduced)
 };
 
 struct FinalArgs {

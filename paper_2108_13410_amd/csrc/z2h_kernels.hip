@@ -785,11 +785,16 @@ __global__ void axpy_kernel(Cx<Real> *y, const Cx<Real> *x, uint64_t n) {
 
 // Per-thread accumulation of one basis' observables for the elements in
 // registers: [0] sum |a|^2, [1] sum |a|^2 (nst - 2k), [2] sum |a|^2 (n - 2w),
-// [3..10] loop parities, [11..11+n] weight histogram (computational basis).
-template <typename Real, int R>
+// [3..10] loop parities.  HIST: lane b of the wave adds the weight of
+// Hamming weight b to hist.  The weights of a wave's elements are those of
+// its first lane plus the set bits of the register and lane indices, so the
+// wave folds its lanes one index bit at a time (a lane with the bit set
+// counts one place higher) and each lane keeps one bin, where a bin per
+// thread took 33 registers pairs and a comparison per bin and element class.
+template <typename Real, int R, bool HIST>
 __device__ __forceinline__ void obs_accum(const Cx<Real> (&v)[1 << R], const LayCtx<R> &L,
                                           int basis, const LatticeDev &lat, const uint32_t *loops,
-                                          int nloops, bool dos, double *acc) {
+                                          int nloops, double *acc, double &hist) {
     uint32_t s = basis ? L.s0x : L.s0z;
     double dl[R + 1];
 #pragma unroll
@@ -818,18 +823,88 @@ __device__ __forceinline__ void obs_accum(const Cx<Real> (&v)[1 << R], const Lay
             if (j < nloops) acc[3 + j] += lp[j] ? -p2 : p2;
         dl[__builtin_popcount(q)] += p2;
     }
-    if (dos) {
+    if constexpr (HIST) {
+        const int lane = threadIdx.x & 63;
+        double c[R + 7];
 #pragma unroll
-        for (int b = 0; b < kDosBins; ++b) {
-            double x = 0.0;
+        for (int j = 0; j <= R; ++j) c[j] = dl[j];
 #pragma unroll
-            for (int j = 0; j <= R; ++j) x += (L.w0 + j == b) ? dl[j] : 0.0;
-            acc[11 + b] += x;
+        for (int b = 0; b < 6; ++b) {
+            const bool up = (lane >> b) & 1;
+            const int deg = R + b;  // highest weight so far
+            c[deg + 1] = 0.0;
+            double prev = 0.0;      // the upper lane's coefficient one below
+#pragma unroll
+            for (int j = 0; j <= R + 6; ++j) {
+                if (j <= deg + 1) {
+                    const double other = __shfl_xor(c[j], 1 << b, 64);
+                    const double lo = up ? other : c[j], hi = up ? c[j] : other;
+                    c[j] = lo + prev;
+                    prev = hi;
+                }
+            }
         }
+        const int w = L.w0 - __builtin_popcount(lane);  // weight of the wave's first lane
+        double x = 0.0;
+#pragma unroll
+        for (int j = 0; j <= R + 6; ++j) x = lane - w == j ? c[j] : x;
+        hist += x;
     }
 }
 
-template <typename Real, int R>
+// Sum over a wave of each of N values a lane holds (N a power of two, at
+// most 64): lane l ends with the sum of value l mod N.  Each step halves the
+// values a lane carries (it gives one half to its partner and keeps the
+// other), so all N sums take N - 1 exchanges (and 6 - log2 N more) where a
+// wave sum per value would take 6 N.
+template <int H, int N>
+__device__ __forceinline__ void halve_sums(double (&v)[N]) {
+    if constexpr (H > 0) {
+        const bool up = threadIdx.x & H;
+#pragma unroll
+        for (int j = 0; j < H; ++j) {
+            const double keep = up ? v[j + H] : v[j], give = up ? v[j] : v[j + H];
+            v[j] = keep + __shfl_xor(give, H, 64);
+        }
+        halve_sums<(H >> 1)>(v);
+    }
+}
+
+template <int N>
+__device__ __forceinline__ double wave_sums(double (&v)[N]) {
+    halve_sums<(N >> 1)>(v);
+    double x = v[0];
+#pragma unroll
+    for (int o = N; o < 64; o <<= 1) x += __shfl_xor(x, o, 64);
+    return x;
+}
+
+// Block sums of every thread's acc (the first 11) and of the waves' bins
+// into out: wave sums, then the waves' rows of LDS in order (deterministic).
+// rows: 64 doubles a wave.
+template <bool HIST>
+__device__ __forceinline__ void block_sums(double (&acc)[16], double hist, double *rows, double *out) {
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    const double x = wave_sums<16>(acc);
+    __syncthreads();
+    if (lane < 11) rows[wv * 64 + lane] = x;
+    if (HIST && lane < kDosBins) rows[wv * 64 + 11 + lane] = hist;
+    __syncthreads();
+    if ((int)threadIdx.x < (HIST ? 11 + kDosBins : 11)) {
+        double s = 0.0;
+        for (int j = 0; j < nw; ++j) s += rows[j * 64 + threadIdx.x];
+        out[threadIdx.x] = s;
+    }
+}
+
+// RED: bit 0: reduce in the computational basis (before the transform),
+// bit 1: in the Hadamard basis (after it).
+//
+// The sums are the kernel's tail: one block sum after another (55 of them,
+// three barriers each) took 48 us on one 2x2 state, 30 us a pass at 3x3 and,
+// at one block per CU, most of the 270 us a pass took at 3x4; all values
+// together they take one wave reduction and two barriers.
+template <typename Real, int R, int RED>
 __global__ void __launch_bounds__(512) obs_kernel(ObsArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const GroupGeom &g = a.geom;
@@ -837,24 +912,21 @@ __global__ void __launch_bounds__(512) obs_kernel(ObsArgs a) {
     const int job = blockIdx.y;
     const uint64_t tiles = 1ull << g.tiles_log2;
     Cx<Real> *lds = reinterpret_cast<Cx<Real> *>(smem);
-    const uint32_t lds_elems = (1u << g.m) + (1u << (g.m - R));
-    double *red = reinterpret_cast<double *>(lds + lds_elems);
     const Cx<Real> *src = reinterpret_cast<const Cx<Real> *>(a.src) + (a.src_off ? a.src_off[job] : 0);
     Cx<Real> *dst = a.dst ? reinterpret_cast<Cx<Real> *>(a.dst) + (a.dst_off ? a.dst_off[job] : 0) : nullptr;
 
-    constexpr int NA = 11 + kDosBins;
-    double accz[NA], accx[11];
+    constexpr bool kZ = RED & 1, kX = RED & 2;
+    static_assert(11 + kDosBins <= 64, "a wave's row of sums");
+    double accz[16], accx[16], hist = 0.0, none = 0.0;
 #pragma unroll
-    for (int j = 0; j < NA; ++j) accz[j] = 0.0;
-#pragma unroll
-    for (int j = 0; j < 11; ++j) accx[j] = 0.0;
+    for (int j = 0; j < 16; ++j) accz[j] = accx[j] = 0.0;
 
     for (uint64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
         Cx<Real> v[1 << R];
         LayCtx<R> L0;
-        lay_ctx<R, true>(L0, g, a.lat, tile, g.p[0], t, a.redZ != 0);
+        lay_ctx<R, true>(L0, g, a.lat, tile, g.p[0], t, kZ, 0);
         load_tile<Real, R, false, true>(v, src, L0);
-        if (a.redZ) obs_accum<Real, R>(v, L0, 0, a.lat, a.zloops, a.nz, true, accz);
+        if constexpr (kZ) obs_accum<Real, R, true>(v, L0, 0, a.lat, a.zloops, a.nz, accz, hist);
         int cur = 0;
         if (a.doH) {
             for (int j = 0; j < g.nlay; ++j) {
@@ -863,66 +935,80 @@ __global__ void __launch_bounds__(512) obs_kernel(ObsArgs a) {
                 cur = j;
             }
         }
-        if (a.redX) {
+        if constexpr (kX) {
             LayCtx<R> Lm;
-            lay_ctx<R, true>(Lm, g, a.lat, tile, g.p[cur], t, true);
-            obs_accum<Real, R>(v, Lm, 1, a.lat, a.xloops, a.nx, false, accx);
+            lay_ctx<R, true>(Lm, g, a.lat, tile, g.p[cur], t, true, 1);
+            obs_accum<Real, R, false>(v, Lm, 1, a.lat, a.xloops, a.nx, accx, none);
         }
         if (dst) {
             if (cur != 0) exchange<Real, R>(v, lds, g.p[cur], g.p[0], t);
             store_tile<Real, R, false, true>(v, dst, L0);
         }
     }
+    // the waves' rows take the exchange region (free: each exchange ends in a barrier)
     const size_t rec = ((size_t)job * gridDim.x + blockIdx.x) * kObsQ;
-    if (a.redZ && a.part_z) {
-        for (int j = 0; j < NA; ++j) {
-            const double s = block_sum(accz[j], red);
-            if (t == 0) a.part_z[rec + j] = s;
-        }
-    }
-    if (a.redX && a.part_x) {
-        for (int j = 0; j < 11; ++j) {
-            const double s = block_sum(accx[j], red);
-            if (t == 0) a.part_x[rec + j] = s;
-        }
-    }
+    double *rows = reinterpret_cast<double *>(smem);
+    if constexpr (kZ) block_sums<true>(accz, hist, rows, a.part_z + rec);
+    if constexpr (kZ && kX) __syncthreads();
+    if constexpr (kX) block_sums<false>(accx, none, rows, a.part_x + rec);
 }
 
-// Sum the per-workgroup records of every job and form the observables.
-__global__ void obs_finalize_kernel(FinalArgs a) {
+// Sum the per-workgroup records of every job and form the observables: 16
+// slices of 64 threads, each thread one value of every 16th record.  (One
+// thread a value over all records, up to 1024 loads in a row, took 97-115 us
+// at 3x3 and 795 us at 3x4.)
+constexpr int kFinalSlices = 16;
+
+__device__ __forceinline__ double final_sum(const double *p, int nrec, int q, int slice) {
+    double s[8] = {};
+    int r = slice;
+    for (; r + 7 * kFinalSlices < nrec; r += 8 * kFinalSlices) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s[j] += p[(size_t)(r + j * kFinalSlices) * kObsQ + q];
+    }
+    for (; r < nrec; r += kFinalSlices) s[0] += p[(size_t)r * kObsQ + q];
+    return ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+}
+
+__global__ void __launch_bounds__(64 * kFinalSlices) obs_finalize_kernel(FinalArgs a) {
     const int job = blockIdx.x;
-    const int t = threadIdx.x;
-    __shared__ double sz[kObsQ], sx[kObsQ];
-    if (t < kObsQ) {
-        double s = 0.0, x = 0.0;
-        const double *pz = a.partZ + (size_t)job * a.nrecZ * kObsQ;
-        const double *px = a.partX + (size_t)job * a.nrecX * kObsQ;
-        for (int r = 0; r < a.nrecZ; ++r) s += pz[(size_t)r * kObsQ + t];
-        for (int r = 0; r < a.nrecX; ++r) x += px[(size_t)r * kObsQ + t];
-        sz[t] = s;
-        sx[t] = x;
+    const int q = threadIdx.x & 63, slice = threadIdx.x >> 6;
+    __shared__ double pz[kFinalSlices][64], px[kFinalSlices][16], sz[64], sx[16];
+    pz[slice][q] = q < 11 + kDosBins ? final_sum(a.partZ + (size_t)job * a.nrecZ * kObsQ, a.nrecZ, q, slice) : 0.0;
+    if (q < 16) px[slice][q] = q < 11 ? final_sum(a.partX + (size_t)job * a.nrecX * kObsQ, a.nrecX, q, slice) : 0.0;
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        double s = 0.0;
+        for (int j = 0; j < kFinalSlices; ++j) s += pz[j][q];
+        sz[q] = s;
+    } else if (threadIdx.x < 80) {
+        double s = 0.0;
+        for (int j = 0; j < kFinalSlices; ++j) s += px[j][q];
+        sx[q] = s;
     }
     __syncthreads();
-    if (t == 0) {
-        const int n = a.n;
-        double *o = a.out + (size_t)(a.out_index ? a.out_index[job] : job) * kObsQ;
+    if (threadIdx.x >= kObsQ) return;
+    const int n = a.n;
+    const double nz = sz[0], nxr = sx[0];
+    double o;
+    if (q == 0) {
+        o = nz;
+    } else if (q <= 5) {
         const double *c = a.H ? a.H + 4 * job : a.H_inline;
-        const double nz = sz[0], nxr = sx[0];
         const double sumB = sz[1] / nz, mz = sz[2] / (n * nz);
         const double sumA = sx[1] / nxr, mx = sx[2] / (n * nxr);
-        o[0] = nz;
-        o[2] = sumA;
-        o[3] = sumB;
-        o[4] = mx;
-        o[5] = mz;
-        o[1] = -c[0] * sumA - c[1] * sumB - c[2] * n * mx - c[3] * n * mz;
-        for (int j = 0; j < kMaxLoops; ++j) {
-            o[6 + j] = sz[3 + j] / nz;
-            o[14 + j] = sx[3 + j] / nxr;
-        }
-        for (int b = 0; b < kDosBins; ++b) o[22 + b] = sz[11 + b] / nz;
-        o[55] = nxr * ldexp(1.0, -n);
+        o = q == 1 ? -c[0] * sumA - c[1] * sumB - c[2] * n * mx - c[3] * n * mz
+                   : q == 2 ? sumA : q == 3 ? sumB : q == 4 ? mx : mz;
+    } else if (q < 14) {
+        o = sz[3 + q - 6] / nz;
+    } else if (q < 22) {
+        o = sx[3 + q - 14] / nxr;
+    } else if (q < 55) {
+        o = sz[11 + q - 22] / nz;
+    } else {
+        o = nxr * ldexp(1.0, -n);
     }
+    a.out[(size_t)(a.out_index ? a.out_index[job] : job) * kObsQ + q] = o;
 }
 
 // ---------------------------------------------------------------- init / misc
@@ -1114,11 +1200,17 @@ static hipError_t do_level(const LevelArgs &a, dim3 grid, size_t lds, hipStream_
 template <typename Real, int R>
 static hipError_t do_obs(const ObsArgs &a, dim3 grid, size_t lds, hipStream_t s) {
     if (a.geom.m - R < 6 || a.geom.m - R > 9) return hipErrorInvalidConfiguration;  // launch bounds
-    const void *fn = reinterpret_cast<const void *>(&obs_kernel<Real, R>);
-    hipError_t e = set_lds(fn, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((obs_kernel<Real, R>), grid, dim3(1u << (a.geom.m - R)), lds, s, a);
-    return hipGetLastError();
+    // what the launch reduces (both at once where one group is the whole transform)
+    auto go = [&](auto kernel) {
+        hipError_t e = set_lds(reinterpret_cast<const void *>(kernel), lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, grid, dim3(1u << (a.geom.m - R)), lds, s, a);
+        return hipGetLastError();
+    };
+    if (a.part_z && a.part_x) return go(&obs_kernel<Real, R, 3>);
+    if (a.part_z) return go(&obs_kernel<Real, R, 1>);
+    if (a.part_x) return go(&obs_kernel<Real, R, 2>);
+    return go(&obs_kernel<Real, R, 0>);
 }
 
 #define Z2H_DISPATCH(FN, ARGS, GRID, LDS, S)                               \
@@ -1147,7 +1239,10 @@ static hipError_t prep_real() {
 #define Z2H_PREP_GEN(r)                                                                                   \
     if (e == hipSuccess) e = set_lds(reinterpret_cast<const void *>(&level_kernel<Real, r, false>), kMaxLdsBytes); \
     if (e == hipSuccess) e = set_lds(reinterpret_cast<const void *>(&level_kernel<Real, r, true>), kMaxLdsBytes);  \
-    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void *>(&obs_kernel<Real, r>), kMaxLdsBytes);
+    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void *>(&obs_kernel<Real, r, 0>), kMaxLdsBytes);       \
+    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void *>(&obs_kernel<Real, r, 1>), kMaxLdsBytes);       \
+    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void *>(&obs_kernel<Real, r, 2>), kMaxLdsBytes);       \
+    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void *>(&obs_kernel<Real, r, 3>), kMaxLdsBytes);
     Z2H_PREP_GEN(2) Z2H_PREP_GEN(3) Z2H_PREP_GEN(4) Z2H_PREP_GEN(5)
 #undef Z2H_PREP_GEN
 #define Z2H_PREP_FULL(r, nl) \
@@ -1199,7 +1294,7 @@ hipError_t launch_obs(bool c128, int R, const ObsArgs &a, unsigned workers, unsi
 }
 
 hipError_t launch_obs_finalize(const FinalArgs &a, unsigned njobs, hipStream_t s) {
-    hipLaunchKernelGGL(obs_finalize_kernel, dim3(njobs), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(obs_finalize_kernel, dim3(njobs), dim3(64 * kFinalSlices), 0, s, a);
     return hipGetLastError();
 }
 
