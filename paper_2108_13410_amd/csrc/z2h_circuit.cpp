@@ -295,6 +295,135 @@ static void fused_limits(int nq, bool c128, int fuse, int *limit, uint64_t *base
     *base = 0;
 }
 
+// The gates of a group as the fine pass applies them.  CNOTs one after
+// another with one target compose (their control masks XOR); between two
+// equal CNOTs with only R_z between them, each R_z whose parity contains the
+// target takes the controls into its parity, and the CNOTs cancel (a gadget
+// becomes one rotation by the parity of its links and the ancilla).
+struct FineGate {
+    GateDev d;
+    uint64_t mask;   // R_z, projection: the qubits whose parity it sees; CNOT: the controls
+    int target;      // H, R_x: the qubit; CNOT: the target
+};
+
+static std::vector<FineGate> fine_gates(const z2h_gate *g, const std::vector<int> &group, int &nh) {
+    std::vector<FineGate> out;
+    for (int i : group) {
+        const z2h_gate &x = g[i];
+        if (x.kind == Z2H_GATE_CNOT) {
+            if (!out.empty() && out.back().d.kind == Z2H_GATE_CNOT && out.back().target == x.q1) {
+                out.back().mask ^= 1ull << x.q0;
+                if (!out.back().mask) out.pop_back();
+            } else {
+                FineGate f;
+                memset(&f, 0, sizeof f);
+                f.d.kind = Z2H_GATE_CNOT;
+                f.mask = 1ull << x.q0;
+                f.target = x.q1;
+                out.push_back(f);
+            }
+            continue;
+        }
+        if (x.kind == Z2H_GATE_H) ++nh;
+        FineGate f;
+        f.d = device_gate(x, 0, 0);
+        const bool diag = x.kind == Z2H_GATE_RZ || x.kind == Z2H_GATE_PROJ0;
+        f.mask = diag ? 1ull << x.q0 : 0ull;
+        f.target = diag ? -1 : x.q0;
+        out.push_back(f);
+    }
+    for (size_t i = 0; i < out.size();) {
+        size_t j = i + 1;
+        if (out[i].d.kind == Z2H_GATE_CNOT) {
+            while (j < out.size() && out[j].d.kind == Z2H_GATE_RZ) ++j;
+            if (j < out.size() && out[j].d.kind == Z2H_GATE_CNOT && out[j].target == out[i].target &&
+                out[j].mask == out[i].mask) {
+                for (size_t k = i + 1; k < j; ++k)
+                    if (out[k].mask >> out[i].target & 1ull) out[k].mask ^= out[i].mask;
+                out.erase(out.begin() + j);
+                out.erase(out.begin() + i);
+                continue;
+            }
+        }
+        ++i;
+    }
+    return out;
+}
+
+// The fine pass over a group (states of at most kFineMaxQubits).  The tile
+// holds the four lowest qubits and those that H, R_x and CNOT targets mix,
+// and is no larger than that or a wave's amplitudes (more tiles, more CUs);
+// all other qubits of the gates may lie outside it.  Phases as in tile_pass.
+static z2h_status fine_pass(int nq, bool c128, void *st, const z2h_gate *g, const std::vector<int> &group,
+                            hipStream_t s) {
+    int nh = 0;
+    const std::vector<FineGate> gates = fine_gates(g, group, nh);
+    if (gates.empty()) return Z2H_OK;
+    uint64_t in = 15ull;
+    for (const FineGate &f : gates)
+        if (f.target >= 0) in |= 1ull << f.target;
+    for (int q = 0; q < nq && __builtin_popcountll(in) < kFineMinTile; ++q) in |= 1ull << q;
+    FusedArgs a;
+    memset(&a, 0, sizeof a);
+    a.state = st;
+    a.nq = nq;
+    a.m = __builtin_popcountll(in);
+    int loc[kMaxCircuitQubits];  // position in the virtual index
+    int nl = 0, nc = 0;
+    for (int q = 0; q < nq; ++q) {
+        if (in >> q & 1ull) {
+            loc[q] = nl;
+            a.lq[nl++] = q;
+        } else {
+            loc[q] = a.m + nc;
+            a.cq[nc++] = q;
+        }
+    }
+    size_t first = 0;
+    std::vector<int> bits;
+    auto close = [&](size_t end) {
+        std::vector<int> lay = bits;
+        for (int b = a.m - 1; (int)lay.size() < kFineBits; --b)
+            if (std::find(lay.begin(), lay.end(), b) == lay.end()) lay.push_back(b);
+        std::sort(lay.begin(), lay.end());
+        uint32_t code = 0;
+        int rb[64];
+        for (int &r : rb) r = -1;
+        for (int b = 0; b < kFineBits; ++b) {
+            code |= (uint32_t)lay[b] << (4 * b);
+            rb[lay[b]] = b;
+        }
+        for (size_t i = first; i < end; ++i) {
+            GateDev d = gates[i].d;
+            d.q0 = d.q1 = d.pad = 0;
+            for (int q = 0; q < nq; ++q) {
+                if (!(gates[i].mask >> q & 1ull)) continue;
+                if (rb[loc[q]] >= 0)
+                    d.q0 |= 1 << rb[loc[q]];
+                else
+                    d.pad |= (int32_t)(1u << loc[q]);
+            }
+            if (gates[i].target >= 0) (d.kind == Z2H_GATE_CNOT ? d.q1 : d.q0) = rb[loc[gates[i].target]];
+            a.gates[a.ngates++] = d;
+        }
+        a.phase[a.nphase++] = code | (uint32_t)a.ngates << 24;
+        first = end;
+        bits.clear();
+    };
+    for (size_t i = 0; i < gates.size(); ++i) {
+        if (gates[i].target < 0) continue;
+        const int b = loc[gates[i].target];
+        if (std::find(bits.begin(), bits.end(), b) != bits.end()) continue;
+        if ((int)bits.size() == kFineBits) close(i);
+        bits.push_back(b);
+    }
+    close(gates.size());
+    a.scale = hadamard_scale(nh);
+    hipError_t e = launch_fine(c128, a, s);
+    if (e != hipSuccess) return fail(Z2H_ERR_HIP, "fused gate pass failed: %s", hipGetErrorString(e));
+    return Z2H_OK;
+}
+
 // One tile-group pass: the tile holds the group's qubits `used`, the four
 // lowest qubits (coalesced rows of 16 amplitudes) and, as padding, the
 // lowest remaining qubits, mloc in all.  Within the group, consecutive gates
@@ -303,6 +432,7 @@ static void fused_limits(int nq, bool c128, int fuse, int *limit, uint64_t *base
 // a phase on the top local bits needs no change of layout.
 static z2h_status tile_pass(int nq, bool c128, void *st, const z2h_gate *g, const std::vector<int> &group,
                             uint64_t used, hipStream_t s) {
+    if (nq <= kFineMaxQubits) return fine_pass(nq, c128, st, g, group, s);
     int mloc;
     uint64_t base;
     fused_limits(nq, c128, 1, &mloc, &base);
@@ -399,7 +529,8 @@ z2h_status run_reg(int nq, bool c128, void *st, double *parts, const z2h_gate *g
         // at least 64 B apart and every line would be assembled from several
         // loads and stores; the tile kernel applies such a group with
         // coalesced rows instead (the group also fits its tile).
-        if ((used & 7ull) == 7ull) return tile_pass(nq, c128, st, g, group, used, s);
+        // Small states: the fine pass (see launch_fine) for every group.
+        if ((used & 7ull) == 7ull || nq <= kFineMaxQubits) return tile_pass(nq, c128, st, g, group, used, s);
         std::vector<char> in(nq, 0);
         std::vector<int> U;
         for (int q = 0; q < nq; ++q)

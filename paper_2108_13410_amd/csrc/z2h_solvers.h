@@ -172,6 +172,22 @@ struct RegArgs {
 };
 static_assert(sizeof(RegArgs) <= 4096, "kernel argument block");
 
+// The fine tile pass (small states): kFineBits register bits, and only the
+// gates that mix amplitudes need their qubit among them.  A gate's bits are
+// positions of the virtual index (tile number << m) | local index; the
+// register bits of its phase are taken out of it.  GateDev there: R_z and
+// the projection act on the parity of the bits pad (outside the registers)
+// and of the register bits q0 (a mask); H and R_x on register bit q0; a
+// CNOT flips register bit q1 with the parity of both masks.
+constexpr int kFineBits = 3;
+constexpr int kFineMinTile = 10;    // a wave's amplitudes
+// Largest state the fine pass takes.  Per Trotter step, before and now, tile
+// groups: 19 qubits complex128 648 -> 286 us, complex64 422 -> 243; 21 qubits
+// 902 -> 461 and 536 -> 382.  Its gain is the code a pass fetches and the
+// waves it has; a larger state runs enough tiles per block to amortize both.
+constexpr int kFineMaxQubits = 22;
+
+hipError_t launch_fine(bool c128, const FusedArgs &a, hipStream_t s);
 hipError_t launch_gate(bool c128, void *state, int nq, const GateDev &g, hipStream_t s);
 hipError_t launch_reg(bool c128, const RegArgs &a, hipStream_t s);
 hipError_t launch_fused(bool c128, const FusedArgs &a, hipStream_t s);
