@@ -1,10 +1,13 @@
 // Whole ramps of small lattices (8 and 12 qubits) inside one workgroup: the
 // state stays in registers from the first step to the last.
 //
-// Each amplitude index is split into register, lane and wave bits.  The
-// register and lane bits are transformed in the wave (z2h_wave.h); the wave
-// bits of the 12-qubit state come into registers through LDS, one exchange
-// each way.  The indices of an element's phase (odd stabilizers, weight) do
+// The lowest six qubits are lane bits, the highest RB qubits register bits,
+// and at 12 qubits the two between them wave bits.  Register and lane bits
+// are transformed in the wave (z2h_wave.h); the wave bits come into the
+// registers through LDS, one exchange each way.  The layers run in the order
+// of the pass kernels' register windows (8-11, 4-7, 0-3 and back from the
+// lowest window; 6-7, 4-5, 2-3, 0-1 at 8 qubits), so that rounding does not
+// depend on how a layer is done.  The indices of an element's phase (odd stabilizers, weight) do
 // not change over the ramp, so every thread keeps its table offsets.
 //
 // What bounds it is the serial chain of one step, not bytes or operations
@@ -14,7 +17,7 @@
 // by three further waves while the first one steps.
 // Measured per step of one state (complex128 / complex64; before, with every
 // layout change through LDS and the tables on the chain: 2.51 / 2.31 us at 8
-// qubits, 8.1 / 4.9 us at 12): 0.89 / 0.72 us and 4.7 / 3.6 us, with
+// qubits, 8.1 / 4.9 us at 12): 0.91 / 0.74 us and 4.9 / 3.7 us, with
 // renormalization 0.17 and 0.3 us more.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -107,8 +110,13 @@ __device__ __forceinline__ void phase(Cx<Real> (&v)[N], const uint32_t (&at)[N],
         const double2 e = tab[at[q]];
         w[q] = Cx<Real>{(Real)(e.x * f), (Real)(e.y * f)};
     }
+    // (the multiply-adds spelled out: every phase rounds alike)
 #pragma unroll
-    for (int q = 0; q < N; ++q) v[q] = cmul(v[q], w[q]);
+    for (int q = 0; q < N; ++q) {
+        const Cx<Real> a = v[q];
+        v[q].x = madd(a.x, w[q].x, -(a.y * w[q].y));
+        v[q].y = madd(a.y, w[q].x, a.x * w[q].y);
+    }
 }
 
 // Butterflies over register bits [lo, hi).
@@ -125,16 +133,59 @@ __device__ __forceinline__ void reg_layers(Cx<Real> (&v)[N]) {
             }
 }
 
-// Exchange of the wave bits with the low WB register bits, through buf.
+// Exchange of the wave bits with the high WB register bits, through buf.
 template <typename S, typename Real>
 __device__ __forceinline__ void wave_exchange(Cx<Real> (&v)[1 << S::RB], Cx<Real> *buf, uint32_t wave, uint32_t lane) {
-    constexpr uint32_t lowm = (1u << S::WB) - 1u;
+    constexpr int keep = S::RB - S::WB;
+    constexpr uint32_t km = (1u << keep) - 1u;
 #pragma unroll
     for (uint32_t q = 0; q < (1u << S::RB); ++q) buf[(((wave << S::RB) | q) << 6) | lane] = v[q];
     __syncthreads();
 #pragma unroll
     for (uint32_t q = 0; q < (1u << S::RB); ++q)
-        v[q] = buf[((((q & lowm) << S::RB) | (q & ~lowm) | wave) << 6) | lane];
+        v[q] = buf[((((q >> keep) << S::RB) | (wave << keep) | (q & km)) << 6) | lane];
+}
+
+// Transform from the layout the state is held in between steps (lane bits
+// 0-5, wave bits above, register bits on top) to the one the x phase meets,
+// and back.
+template <typename S, typename Real>
+__device__ __forceinline__ void to_x(Cx<Real> (&v)[1 << S::RB], Cx<Real> *buf, uint32_t wave, uint32_t lane, uint32_t lam) {
+    reg_layers<0, S::RB>(v);
+    lane_layer<4, true, 0>(v, lam);
+    lane_layer<5, true, 1>(v, lam);
+    if constexpr (S::WB != 0) {
+        wave_exchange<S, Real>(v, buf, wave, lane);
+        reg_layers<S::RB - S::WB, S::RB>(v);
+        row_layers<0, 4, true>(v, lam);
+    } else {
+        row_layers<2, 4, true>(v, lam);
+        row_layers<0, 2, true>(v, lam);
+    }
+}
+
+template <typename S, typename Real>
+__device__ __forceinline__ void from_x(Cx<Real> (&v)[1 << S::RB], Cx<Real> *buf, uint32_t wave, uint32_t lane, uint32_t lam) {
+    row_layers<0, 4, false>(v, lam);
+    lane_layer<4, false, 0>(v, lam);
+    lane_layer<5, false, 1>(v, lam);
+    if constexpr (S::WB != 0) {
+        reg_layers<S::RB - S::WB, S::RB>(v);
+        wave_exchange<S, Real>(v, buf, wave, lane);
+    }
+    reg_layers<0, S::RB>(v);
+}
+
+// Index of register element q of a thread at the x phase.
+template <typename S>
+__device__ __forceinline__ uint32_t x_index(uint32_t wave, uint32_t lam, uint32_t q) {
+    constexpr int keep = S::RB - S::WB;
+    const uint32_t w = S::WB ? q >> keep : 0u;                                   // wave bits, in the registers
+    const uint32_t e = S::WB ? (wave << keep) | (q & ((1u << keep) - 1u)) : q;   // element before the exchange
+    // before it, lane bits 4 and 5 traded places with element bits 0 and 1
+    const uint32_t lo = (lam & 15u) | ((e & 1u) << 4) | ((e & 2u) << 4);
+    const uint32_t el = (e & ~3u) | ((lam >> 4) & 3u);
+    return lo | (w << 6) | (el << (6 + S::WB));
 }
 
 template <typename S, typename Real>
@@ -152,17 +203,14 @@ __global__ void __launch_bounds__(S::threads) resident_kernel(ResidentArgs a) {
     Cx<Real> v[N];
     uint32_t atz[N], atx[N];
     Cx<Real> *st = reinterpret_cast<Cx<Real> *>(a.states) + J.offset;
-    const uint32_t base = (wave << (6 + S::RB)) | lam;
+    const uint32_t base = (wave << 6) | lam;
     if (steps) {
 #pragma unroll
         for (int q = 0; q < N; ++q) {
-            v[q] = st[base | ((uint32_t)q << 6)];
-            atz[q] = table_index<S>(a.lat.zmask, base | ((uint32_t)q << 6));
-            // the x phase meets the state after the wave exchange
-            constexpr uint32_t lowm = (1u << S::WB) - 1u;
-            const uint32_t e = ((uint32_t)q & ~lowm) | (wave & lowm);
-            const uint32_t ix = lane_layers_index(lam, e) | (((uint32_t)q & lowm) << (6 + S::RB));
-            atx[q] = table_index<S>(a.lat.xmask, ix);
+            const uint32_t i = base | ((uint32_t)q << (6 + S::WB));
+            v[q] = st[i];
+            atz[q] = table_index<S>(a.lat.zmask, i);
+            atx[q] = table_index<S>(a.lat.xmask, x_index<S>(wave, lam, (uint32_t)q));
         }
     }
     const bool use_norms = J.renorm || J.norm_trace;
@@ -182,29 +230,19 @@ __global__ void __launch_bounds__(S::threads) resident_kernel(ResidentArgs a) {
             phase<Real, N>(v, atz, tab, 1.0);
             return;
         }
-        reg_layers<0, S::RB>(v);
-        lane_layers<true>(v, lam);
+        to_x<S, Real>(v, L.ex[0], wave, lane, lam);
         double f = 1.0;
-        if constexpr (S::WB != 0) {
-            wave_exchange<S, Real>(v, L.ex[0], wave, lane);
-            if (have_norm) {
+        if (have_norm) {
+            if constexpr (S::WB != 0) {
                 norm = 0.0;
                 for (int j = 0; j < S::step_waves; ++j) norm += L.red[j];
             }
-            reg_layers<0, S::WB>(v);
-        }
-        if (have_norm) {
             if (threadIdx.x == 0 && J.norm_trace)
                 gst(J.norm_trace, J.order == 0 ? p / 2 - 1 : p / 2, norm);
             if (J.renorm) f = 1.0 / sqrt(norm);
         }
         phase<Real, N>(v, atx, tab, f);
-        if constexpr (S::WB != 0) {
-            reg_layers<0, S::WB>(v);
-            wave_exchange<S, Real>(v, L.ex[1], wave, lane);
-        }
-        lane_layers<false>(v, lam);
-        reg_layers<0, S::RB>(v);
+        from_x<S, Real>(v, L.ex[S::WB ? 1 : 0], wave, lane, lam);
     };
 
     if constexpr (S::PW != 0) {
@@ -232,7 +270,7 @@ __global__ void __launch_bounds__(S::threads) resident_kernel(ResidentArgs a) {
     }
     if (steps) {
 #pragma unroll
-        for (int q = 0; q < N; ++q) st[base | ((uint32_t)q << 6)] = v[q];
+        for (int q = 0; q < N; ++q) st[base | ((uint32_t)q << (6 + S::WB))] = v[q];
     }
 }
 

@@ -35,6 +35,9 @@ __device__ __forceinline__ double lane_across(double x) {
     return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
 }
 
+__device__ __forceinline__ float madd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double madd(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 // Exchange of the lane bit of direction B (4 or 5) with the register bit
 // that tells a from b: a keeps its lower lanes and takes b's, b the upper.
 template <int B>
@@ -87,7 +90,8 @@ __device__ __forceinline__ void fmac4_across(float &a, float &b, float &c, float
 #undef Z2H_FMAC4
 }
 
-// One butterfly layer along lane direction B of every register element.
+// One butterfly layer along lane direction B of every register element;
+// directions 5 and 4 trade places with register bit T.
 //
 // Within a row the partner's value comes with the multiply-add itself: a
 // lane forms own + s other with s = -1 in the upper lanes, which leaves the
@@ -95,7 +99,7 @@ __device__ __forceinline__ void fmac4_across(float &a, float &b, float &c, float
 // its way back meet that sign twice: FWD leaves it, !FWD takes a vector that
 // carries it (s = +1 in the upper lanes).  Every product with s is exact, so
 // the sums are those of the plain butterfly.
-template <int B, bool FWD, typename Real, int N>
+template <int B, bool FWD, int T = 0, typename Real, int N>
 __device__ __forceinline__ void lane_layer(Cx<Real> (&v)[N], uint32_t lam) {
     if constexpr (B < 4) {
         const Real s = (((lam >> B) & 1u) != 0) == FWD ? (Real)-1 : (Real)1;
@@ -110,8 +114,8 @@ __device__ __forceinline__ void lane_layer(Cx<Real> (&v)[N], uint32_t lam) {
             }
         }
     } else {
-        // direction 5 trades places with register bit 0, direction 4 with bit 1
-        constexpr int r = B == 5 ? 1 : 2;
+        constexpr int r = 1 << T;
+        static_assert(N > r, "the register bit that trades places");
         auto swap = [&]() {
 #pragma unroll
             for (int q = 0; q < N; ++q)
@@ -132,47 +136,27 @@ __device__ __forceinline__ void lane_layer(Cx<Real> (&v)[N], uint32_t lam) {
     }
 }
 
-// All six directions; FWD as above.  Forward, lane bits 5 and 4 end in
-// register bits 0 and 1 (and those in the lanes); the way back starts there.
-template <bool FWD, typename Real, int N>
-__device__ __forceinline__ void lane_layers(Cx<Real> (&v)[N], uint32_t lam) {
-    static_assert(N % 4 == 0, "two register bits trade places with lane bits");
-    if constexpr (FWD) {
-        lane_layer<5, true>(v, lam);
-        lane_layer<4, true>(v, lam);
-        lane_layer<3, true>(v, lam);
-        lane_layer<2, true>(v, lam);
-        lane_layer<1, true>(v, lam);
-        lane_layer<0, true>(v, lam);
-    } else {
-        lane_layer<0, false>(v, lam);
-        lane_layer<1, false>(v, lam);
-        lane_layer<2, false>(v, lam);
-        lane_layer<3, false>(v, lam);
-        lane_layer<4, false>(v, lam);
-        lane_layer<5, false>(v, lam);
+// Directions [LO, HI) below 4, lowest first.
+template <int LO, int HI, bool FWD, typename Real, int N>
+__device__ __forceinline__ void row_layers(Cx<Real> (&v)[N], uint32_t lam) {
+    if constexpr (LO < HI) {
+        lane_layer<LO, FWD>(v, lam);
+        row_layers<LO + 1, HI, FWD>(v, lam);
     }
 }
 
-// Index (lane bits 0-5, register bits above) of register element q of a lane
-// after the forward layers.
-__device__ __forceinline__ uint32_t lane_layers_index(uint32_t lam, uint32_t q) {
-    return (lam & 15u) | ((q & 2u) << 3) | ((q & 1u) << 5) | (((lam >> 5) & 1u) << 6) | (((lam >> 4) & 1u) << 7) |
-           ((q & ~3u) << 6);
-}
-
-// Wave sum, every lane (row exchanges by DPP, then the row and half swaps).
+// Wave sum, every lane, over the logical lane bits from the highest down.
 __device__ __forceinline__ double wave_sum_lanes(double x) {
-    x += lane_across<0>(x);
-    x += lane_across<1>(x);
-    x += lane_across<2>(x);
-    x += lane_across<3>(x);
     double y = x;
-    lane_swap<4>(x, y);
+    lane_swap<5>(x, y);
     x += y;
     y = x;
-    lane_swap<5>(x, y);
-    return x + y;
+    lane_swap<4>(x, y);
+    x += y;
+    x += lane_across<3>(x);
+    x += lane_across<2>(x);
+    x += lane_across<1>(x);
+    return x + lane_across<0>(x);
 }
 
 }  // namespace z2h
