@@ -150,10 +150,14 @@ __device__ __forceinline__ int reg_bit(const LayCtx<R> &L, int r) {
     return r < L.nlo ? L.gs + r : L.gs2 + (r - L.nlo);
 }
 
-__device__ __forceinline__ uint32_t syndrome_direct(const uint32_t *masks, int nst, uint64_t i) {
+// Masks past the lattice's last stabilizer are zero: all kMaxStab of them are
+// fetched at once and taken without a branch.  (A loop over the lattice's own
+// waits for one scalar load per mask: 1500 cycles of a 3x3 pass.)
+__device__ __forceinline__ uint32_t syndrome_direct(const uint32_t *masks, uint64_t i) {
     uint32_t s = 0;
     const uint32_t ii = (uint32_t)i;
-    for (int k = 0; k < nst; ++k) s |= (uint32_t)(popc(ii & masks[k]) & 1) << k;
+#pragma unroll
+    for (int k = 0; k < kMaxStab; ++k) s |= (uint32_t)(popc(ii & masks[k]) & 1) << k;
     return s;
 }
 
@@ -174,8 +178,8 @@ __device__ __forceinline__ void lay_ctx(LayCtx<R> &L, const GroupGeom &g, const 
     }
     L.w0 = __builtin_popcountll(L.i0);
     if (want_syn) {
-        L.s0z = which != 1 ? syndrome_direct(lat.zmask, lat.nst, L.i0) : 0u;
-        L.s0x = which != 0 ? syndrome_direct(lat.xmask, lat.nst, L.i0) : 0u;
+        L.s0z = which != 1 ? syndrome_direct(lat.zmask, L.i0) : 0u;
+        L.s0x = which != 0 ? syndrome_direct(lat.xmask, L.i0) : 0u;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int b = SPLIT ? reg_bit(L, r) : L.gs + r;
