@@ -250,53 +250,53 @@ double tridiag_lowest(const double *a, const double *b, int m) {
 }
 
 // Eigen-decomposition of the symmetric tridiagonal T (diagonal a[0..m),
-// off-diagonal b[1..m)) by cyclic Jacobi rotations: T = Q diag(lam) Q^T,
-// Q row-major (column l is the eigenvector of lam[l]).
+// off-diagonal b[1..m)) by implicit QR steps with Wilkinson's shift (Golub
+// and Van Loan, Matrix Computations, sec. 8.3): T = Q diag(lam) Q^T, Q
+// row-major (column l is the eigenvector of lam[l]).  The host waits for it
+// between two steps of the exact evolution: cyclic Jacobi sweeps over the
+// full matrix took 0.5 ms of each step at m = 16, with the GPU idle (3x3: 20
+// steps 21.9 -> 11.4 ms).
 void tridiag_eigs(const double *a, const double *b, int m, std::vector<double> &lam, std::vector<double> &Q) {
-    std::vector<double> A((size_t)m * m, 0.0);
-    Q.assign((size_t)m * m, 0.0);
-    for (int i = 0; i < m; ++i) {
-        A[(size_t)i * m + i] = a[i];
-        if (i > 0) A[(size_t)i * m + i - 1] = A[(size_t)(i - 1) * m + i] = b[i];
-        Q[(size_t)i * m + i] = 1.0;
-    }
-    for (int sweep = 0; sweep < 100; ++sweep) {
-        double off = 0.0, tot = 0.0;
-        for (int i = 0; i < m; ++i)
-            for (int j = 0; j < m; ++j) {
-                const double v = A[(size_t)i * m + j] * A[(size_t)i * m + j];
-                tot += v;
-                if (i != j) off += v;
+    lam.assign(a, a + m);
+    std::vector<double> e((size_t)m, 0.0);  // e[i] couples i and i + 1
+    for (int i = 0; i + 1 < m; ++i) e[i] = b[i + 1];
+    Q.assign((size_t)m * m, 0.0);  // transposed while it is built: row l is column l
+    for (int i = 0; i < m; ++i) Q[(size_t)i * m + i] = 1.0;
+    double *d = lam.data();
+    const double eps = 1.1e-16;
+    int hi = m - 1;
+    for (int step = 0; hi > 0 && step < 60 * m; ++step) {
+        int lo = hi;
+        while (lo > 0 && std::fabs(e[lo - 1]) > eps * (std::fabs(d[lo - 1]) + std::fabs(d[lo]))) --lo;
+        if (lo == hi) {
+            --hi;
+            continue;
+        }
+        const double h = 0.5 * (d[hi - 1] - d[hi]), f = e[hi - 1];
+        const double mu = d[hi] - f * f / (h + std::copysign(std::hypot(h, f), h));
+        double x = d[lo] - mu, z = e[lo];
+        for (int k = lo; k < hi; ++k) {
+            const double r = std::hypot(x, z), c = r > 0.0 ? x / r : 1.0, s = r > 0.0 ? z / r : 0.0;
+            if (k > lo) e[k - 1] = r;
+            const double d1 = d[k], d2 = d[k + 1], ek = e[k], t = 2.0 * c * s * ek;
+            d[k] = c * c * d1 + t + s * s * d2;
+            d[k + 1] = s * s * d1 - t + c * c * d2;
+            e[k] = c * s * (d2 - d1) + (c * c - s * s) * ek;
+            if (k + 1 < hi) {
+                x = e[k];
+                z = s * e[k + 1];
+                e[k + 1] *= c;
             }
-        if (off <= 1e-32 * tot || off == 0.0) break;
-        for (int p = 0; p < m; ++p)
-            for (int q = p + 1; q < m; ++q) {
-                const double apq = A[(size_t)p * m + q];
-                if (apq == 0.0) continue;
-                const double app = A[(size_t)p * m + p], aqq = A[(size_t)q * m + q];
-                // rotation angle that zeroes A[p][q]
-                const double theta = (aqq - app) / (2.0 * apq);
-                const double t = (theta >= 0 ? 1.0 : -1.0) / (std::fabs(theta) + std::sqrt(theta * theta + 1.0));
-                const double c = 1.0 / std::sqrt(t * t + 1.0), s = t * c;
-                for (int k = 0; k < m; ++k) {
-                    const double akp = A[(size_t)k * m + p], akq = A[(size_t)k * m + q];
-                    A[(size_t)k * m + p] = c * akp - s * akq;
-                    A[(size_t)k * m + q] = s * akp + c * akq;
-                }
-                for (int k = 0; k < m; ++k) {
-                    const double apk = A[(size_t)p * m + k], aqk = A[(size_t)q * m + k];
-                    A[(size_t)p * m + k] = c * apk - s * aqk;
-                    A[(size_t)q * m + k] = s * apk + c * aqk;
-                }
-                for (int k = 0; k < m; ++k) {
-                    const double qkp = Q[(size_t)k * m + p], qkq = Q[(size_t)k * m + q];
-                    Q[(size_t)k * m + p] = c * qkp - s * qkq;
-                    Q[(size_t)k * m + q] = s * qkp + c * qkq;
-                }
+            double *q0 = &Q[(size_t)k * m], *q1 = q0 + m;
+            for (int i = 0; i < m; ++i) {
+                const double u = q0[i], v = q1[i];
+                q0[i] = c * u + s * v;
+                q1[i] = c * v - s * u;
             }
+        }
     }
-    lam.resize((size_t)m);
-    for (int l = 0; l < m; ++l) lam[l] = A[(size_t)l * m + l];
+    for (int i = 0; i < m; ++i)
+        for (int j = i + 1; j < m; ++j) std::swap(Q[(size_t)i * m + j], Q[(size_t)j * m + i]);
 }
 
 // Eigenvector of the lowest eigenvalue theta of T (diagonal a[0..m),
