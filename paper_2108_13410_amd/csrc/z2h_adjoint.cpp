@@ -49,6 +49,23 @@ static z2h_status adj_launch(const Plan &P, AdjArgs &a, int group, hipStream_t s
     return Z2H_OK;
 }
 
+// A half block per state: groups in one run of qubits whose layout changes
+// exchange whole elements, with at most 256 threads a tile (two register
+// files of a larger one would not fit) and room for two tiles in LDS.
+static size_t pair_lds(const Plan &P, const GroupGeom &g) {
+    return 2 * ((size_t)1 << (g.m - g.R * g.full)) * (size_t)g.lds_blk * P.esize +
+           (((size_t)(P.nst + 1) * (P.n + 1) * P.esize + 31) & ~(size_t)15) + 16 * sizeof(double);
+}
+
+static bool pair_ok(const Plan &P) {
+    if (P.K < 2) return false;
+    for (int j = 0; j < P.K; ++j) {
+        const GroupGeom &g = P.geom[j];
+        if (!g.full || !g.lds_blk || g.cx || g.hi || g.m - g.R > 8 || pair_lds(P, g) > (size_t)kMaxLdsBytes) return false;
+    }
+    return true;
+}
+
 extern "C" z2h_status z2h_adjoint(const z2h_plan *plan, const void *d_psi_final, void *d_ws, size_t ws_bytes,
                                   const z2h_schedule *sched, const z2h_couplings *lossH, double *d_gradZ,
                                   double *d_gradX, double *h_loss, void *stream) {
@@ -83,7 +100,7 @@ extern "C" z2h_status z2h_adjoint(const z2h_plan *plan, const void *d_psi_final,
         void *C = c.take(sb);
         size_t maxtiles = 1;
         for (int g = 0; g < P.K; ++g) maxtiles = std::max(maxtiles, (size_t)1 << P.geom[g].tiles_log2);
-        double *part = (double *)c.take(sizeof(double) * maxtiles);
+        (void)c.take(sizeof(double) * maxtiles);  // (a level's partials, now in the scratch state)
         double *rec = (double *)c.take(sizeof(double) * kObsQ * obs_records(P));
         double *obs_out = (double *)c.take(sizeof(double) * kObsQ);
         double *dsz = (double *)c.take(sizeof(double) * S);
@@ -164,41 +181,71 @@ extern "C" z2h_status z2h_adjoint(const z2h_plan *plan, const void *d_psi_final,
         hipError_t e = launch_axpy(P.c128, B, C, 1ull << P.n, s);
         if (e != hipSuccess) return fail(Z2H_ERR_HIP, "axpy launch failed: %s", hipGetErrorString(e));
 
-        // reverse sweep over the forward levels
-        for (int lev = nlev - 1; lev >= 0; --lev) {
-            const LevelOp op = level_op_host(lev, Kq, S, 0, 0);
-            if (op.kind == kIdle) continue;
-            if (K == 1 && op.kind == kPlainH) continue;  // one-group plans transform inside the x pass
-            AdjArgs r;
-            memset(&r, 0, sizeof r);
-            r.job = J;
-            r.op = op;
-            r.A = A;
-            r.B = B;
-            const int group = K == 1 ? 0 : op.group;
-            if (op.kind == kPlainH) {
-                r.mode = 0;
-                if ((st = adj_launch(P, r, group, s))) return st;
-                continue;
+        // reverse sweep over the forward levels, in chunks: the scratch state
+        // (free from here on) holds a chunk's block partials, summed by one
+        // launch, and its phase tables for the pair kernel
+        const bool pair = pair_ok(P);
+        const size_t tab_bytes = pair ? (size_t)(P.nst + 1) * (P.n + 1) * P.esize : 0;
+        const int chunk = (int)std::min<size_t>((size_t)nlev, sb / (tab_bytes + sizeof(double) * maxtiles));
+        if (chunk < 1) return fail(Z2H_ERR_UNSUPPORTED, "no room for a level's partials");
+        double *parts = (double *)C;
+        unsigned char *tabs = (unsigned char *)C + sizeof(double) * maxtiles * (size_t)chunk;
+        for (int hi = nlev; hi > 0; hi -= chunk) {
+            const int lo = std::max(0, hi - chunk);
+            if (pair) {
+                TablesArgs ta;
+                memset(&ta, 0, sizeof ta);
+                ta.tabs = tabs;
+                ta.job = J;
+                ta.lat = P.lat;
+                ta.lev0 = lo;
+                ta.K = Kq;
+                e = launch_tables(P.c128, ta, (unsigned)(hi - lo), s);
+                if (e != hipSuccess) return fail(Z2H_ERR_HIP, "table kernel launch failed: %s", hipGetErrorString(e));
             }
-            r.mode = 1;
-            r.no_transform = (K == 1 && op.basis == 0) ? 1 : 0;
-            // dH/ds in the level's basis
-            if (op.basis == 0) {
-                r.dJ = -(sched->end.JB - sched->start.JB);
-                r.dh = -(sched->end.hz - sched->start.hz);
-            } else {
-                r.dJ = -(sched->end.JA - sched->start.JA);
-                r.dh = -(sched->end.hx - sched->start.hx);
+            for (int lev = hi - 1; lev >= lo; --lev) {
+                const LevelOp op = level_op_host(lev, Kq, S, 0, 0);
+                if (op.kind == kIdle) continue;
+                if (K == 1 && op.kind == kPlainH) continue;  // one-group plans transform inside the x pass
+                AdjArgs r;
+                memset(&r, 0, sizeof r);
+                r.job = J;
+                r.op = op;
+                r.A = A;
+                r.B = B;
+                const int group = K == 1 ? 0 : op.group;
+                r.mode = op.kind == kPlainH ? 0 : 1;
+                r.no_transform = (K == 1 && op.basis == 0) ? 1 : 0;
+                // dH/ds in the level's basis
+                if (op.basis == 0) {
+                    r.dJ = -(sched->end.JB - sched->start.JB);
+                    r.dh = -(sched->end.hz - sched->start.hz);
+                } else {
+                    r.dJ = -(sched->end.JA - sched->start.JA);
+                    r.dh = -(sched->end.hx - sched->start.hx);
+                }
+                r.part = parts + (size_t)(lev - lo) * maxtiles;
+                if (!pair) {
+                    if ((st = adj_launch(P, r, group, s))) return st;
+                    continue;
+                }
+                r.tab = tabs + (size_t)(lev - lo) * tab_bytes;
+                r.geom = P.geom[group];
+                r.lat = P.lat;
+                e = launch_adj_pair(P.c128, r, 1u << r.geom.tiles_log2, pair_lds(P, r.geom), s);
+                if (e != hipSuccess) return fail(Z2H_ERR_HIP, "adjoint kernel launch failed: %s", hipGetErrorString(e));
             }
-            r.part = part;
-            if ((st = adj_launch(P, r, group, s))) return st;
             AdjFinalArgs f;
             memset(&f, 0, sizeof f);
-            f.part = part;
-            f.np = 1 << P.geom[group].tiles_log2;
-            f.out = level_sum + lev;
-            e = launch_adj_final(f, s);
+            f.part = parts;
+            f.stride = maxtiles;
+            f.lev0 = lo;
+            f.K = Kq;
+            f.S = S;
+            f.np_z = 1 << P.geom[0].tiles_log2;
+            f.np_x = 1 << P.geom[K - 1].tiles_log2;
+            f.out = level_sum;
+            e = launch_adj_final(f, (unsigned)(hi - lo), s);
             if (e != hipSuccess) return fail(Z2H_ERR_HIP, "adjoint reduction failed: %s", hipGetErrorString(e));
         }
         AdjGradArgs gr;

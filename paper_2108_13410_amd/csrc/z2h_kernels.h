@@ -108,13 +108,16 @@ struct AdjArgs {
     double dJ, dh;             // diagonal (nst - 2k) dJ + (n - 2w) dh: gradient weight (mode 1) or energy (mode 2)
     double dscale;             // extra real factor of the mode-2 diagonal (2^-n in the Hadamard basis)
     double *part;              // per-block partial sums of Im sum conj(B) D A (mode 1)
+    const void *tab;           // forward phase table of the level (the pair kernel, mode 1)
 };
 
 struct AdjFinalArgs {
-    const double *part;        // per-block partials of one level
-    int32_t np;                // number of partials
+    const double *part;        // per-block partials of level lev0, the next level's stride doubles on
+    uint64_t stride;
+    int32_t lev0, K, S;        // of the x-z-x level sequence
+    int32_t np_z, np_x;        // partials of a level in either basis
     int32_t pad;
-    double *out;               // the level's sum
+    double *out;               // level lev's sum at out[lev]
 };
 
 struct AdjGradArgs {
@@ -125,7 +128,8 @@ struct AdjGradArgs {
 };
 
 hipError_t launch_adj(bool c128, const AdjArgs &a, unsigned nblocks, size_t lds, hipStream_t s);
-hipError_t launch_adj_final(const AdjFinalArgs &a, hipStream_t s);
+hipError_t launch_adj_pair(bool c128, const AdjArgs &a, unsigned nblocks, size_t lds, hipStream_t s);
+hipError_t launch_adj_final(const AdjFinalArgs &a, unsigned nlevels, hipStream_t s);
 hipError_t launch_adj_grad(const AdjGradArgs &a, hipStream_t s);
 hipError_t launch_axpy(bool c128, void *y, const void *x, uint64_t n, hipStream_t s);
 bool adj_shape_ok(int R, int NL);
