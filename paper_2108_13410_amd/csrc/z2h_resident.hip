@@ -119,73 +119,21 @@ __device__ __forceinline__ void phase(Cx<Real> (&v)[N], const uint32_t (&at)[N],
     }
 }
 
-// Butterflies over register bits [lo, hi).
-template <int LO, int HI, typename Real, int N>
-__device__ __forceinline__ void reg_layers(Cx<Real> (&v)[N]) {
+// Sum of |v|^2 over a thread's elements, pairwise in the storage precision.
+// The first IM elements take the form abs2<true>: three in the x-z-x order
+// at 12 qubits, none elsewhere, which are the sums (to the last bit) that
+// renormalized complex64 ramps have been scaled by.
+template <int IM, typename Real, int N>
+__device__ __forceinline__ double reg_norm(const Cx<Real> (&v)[N]) {
+    Real a[N];
 #pragma unroll
-    for (int j = LO; j < HI; ++j)
+    for (int q = 0; q < N; ++q) a[q] = q < IM ? abs2<true>(v[q]) : abs2<false>(v[q]);
 #pragma unroll
-        for (int q = 0; q < N; ++q)
-            if (!(q & (1 << j))) {
-                const Cx<Real> a = v[q], b = v[q | (1 << j)];
-                v[q] = cadd(a, b);
-                v[q | (1 << j)] = csub(a, b);
-            }
-}
-
-// Exchange of the wave bits with the high WB register bits, through buf.
-template <typename S, typename Real>
-__device__ __forceinline__ void wave_exchange(Cx<Real> (&v)[1 << S::RB], Cx<Real> *buf, uint32_t wave, uint32_t lane) {
-    constexpr int keep = S::RB - S::WB;
-    constexpr uint32_t km = (1u << keep) - 1u;
+    for (int h = N >> 1; h > 0; h >>= 1) {
 #pragma unroll
-    for (uint32_t q = 0; q < (1u << S::RB); ++q) buf[(((wave << S::RB) | q) << 6) | lane] = v[q];
-    __syncthreads();
-#pragma unroll
-    for (uint32_t q = 0; q < (1u << S::RB); ++q)
-        v[q] = buf[((((q >> keep) << S::RB) | (wave << keep) | (q & km)) << 6) | lane];
-}
-
-// Transform from the layout the state is held in between steps (lane bits
-// 0-5, wave bits above, register bits on top) to the one the x phase meets,
-// and back.
-template <typename S, typename Real>
-__device__ __forceinline__ void to_x(Cx<Real> (&v)[1 << S::RB], Cx<Real> *buf, uint32_t wave, uint32_t lane, uint32_t lam) {
-    reg_layers<0, S::RB>(v);
-    lane_layer<4, true, 0>(v, lam);
-    lane_layer<5, true, 1>(v, lam);
-    if constexpr (S::WB != 0) {
-        wave_exchange<S, Real>(v, buf, wave, lane);
-        reg_layers<S::RB - S::WB, S::RB>(v);
-        row_layers<0, 4, true>(v, lam);
-    } else {
-        row_layers<2, 4, true>(v, lam);
-        row_layers<0, 2, true>(v, lam);
+        for (int q = 0; q < h; ++q) a[q] += a[q + h];
     }
-}
-
-template <typename S, typename Real>
-__device__ __forceinline__ void from_x(Cx<Real> (&v)[1 << S::RB], Cx<Real> *buf, uint32_t wave, uint32_t lane, uint32_t lam) {
-    row_layers<0, 4, false>(v, lam);
-    lane_layer<4, false, 0>(v, lam);
-    lane_layer<5, false, 1>(v, lam);
-    if constexpr (S::WB != 0) {
-        reg_layers<S::RB - S::WB, S::RB>(v);
-        wave_exchange<S, Real>(v, buf, wave, lane);
-    }
-    reg_layers<0, S::RB>(v);
-}
-
-// Index of register element q of a thread at the x phase.
-template <typename S>
-__device__ __forceinline__ uint32_t x_index(uint32_t wave, uint32_t lam, uint32_t q) {
-    constexpr int keep = S::RB - S::WB;
-    const uint32_t w = S::WB ? q >> keep : 0u;                                   // wave bits, in the registers
-    const uint32_t e = S::WB ? (wave << keep) | (q & ((1u << keep) - 1u)) : q;   // element before the exchange
-    // before it, lane bits 4 and 5 traded places with element bits 0 and 1
-    const uint32_t lo = (lam & 15u) | ((e & 1u) << 4) | ((e & 2u) << 4);
-    const uint32_t el = (e & ~3u) | ((lam >> 4) & 3u);
-    return lo | (w << 6) | (el << (6 + S::WB));
+    return (double)a[0];
 }
 
 template <typename S, typename Real>
@@ -210,7 +158,7 @@ __global__ void __launch_bounds__(S::threads) resident_kernel(ResidentArgs a) {
             const uint32_t i = base | ((uint32_t)q << (6 + S::WB));
             v[q] = st[i];
             atz[q] = table_index<S>(a.lat.zmask, i);
-            atx[q] = table_index<S>(a.lat.xmask, x_index<S>(wave, lam, (uint32_t)q));
+            atx[q] = table_index<S>(a.lat.xmask, wave_index<S::RB, S::WB>(wave, lam, (uint32_t)q));
         }
     }
     const bool use_norms = J.renorm || J.norm_trace;
@@ -222,7 +170,7 @@ __global__ void __launch_bounds__(S::threads) resident_kernel(ResidentArgs a) {
         if ((lev & 1) == 0) {  // computational basis
             const bool meas = use_norms && (J.order == 0 || p < nph - 1);
             if (meas) {
-                const double s = wave_sum_lanes(sumsq<Real, S::RB>(v));
+                const double s = wave_sum_lanes(S::WB && J.order == 0 ? reg_norm<3>(v) : reg_norm<0>(v));
                 if constexpr (S::WB == 0) norm = s;
                 else if (lane == 0) L.red[wave] = s;  // read after the next exchange's barrier
                 have_norm = true;
@@ -230,7 +178,7 @@ __global__ void __launch_bounds__(S::threads) resident_kernel(ResidentArgs a) {
             phase<Real, N>(v, atz, tab, 1.0);
             return;
         }
-        to_x<S, Real>(v, L.ex[0], wave, lane, lam);
+        fwd_wave<S::RB, S::WB, false>(v, L.ex[0], wave, lane, lam);
         double f = 1.0;
         if (have_norm) {
             if constexpr (S::WB != 0) {
@@ -242,7 +190,7 @@ __global__ void __launch_bounds__(S::threads) resident_kernel(ResidentArgs a) {
             if (J.renorm) f = 1.0 / sqrt(norm);
         }
         phase<Real, N>(v, atx, tab, f);
-        from_x<S, Real>(v, L.ex[S::WB ? 1 : 0], wave, lane, lam);
+        bwd_wave<S::RB, S::WB, false>(v, L.ex[S::WB ? 1 : 0], wave, lane, lam);
     };
 
     if constexpr (S::PW != 0) {

@@ -1,5 +1,6 @@
-// Job records, schedule values, phase angles and the level sequence on the
-// device, shared by the pass kernels and the one-workgroup kernel.
+// Job records, schedule values, phase angles and tables and the level
+// sequence on the device, shared by the pass kernels and the one-workgroup
+// kernel.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -8,6 +9,75 @@
 #include "z2h_tile.h"
 
 namespace z2h {
+
+// FP64 factors of the phase table live at the start of the exchange
+// region: every kernel builds its table while no layout change is in flight
+// (before the first exchange of a pass, or after the closing barrier of the
+// last one), and the region (at least 2^8 elements) outsizes the factors.
+__device__ __forceinline__ double2 *table_scratch(unsigned char *smem) {
+    return reinterpret_cast<double2 *>(smem);
+}
+
+// Build the phase table T[k][w] = scale * exp(i (alpha (nst - 2k) + beta (n - 2w)))
+// in LDS (FP64 angles and products, cast to Real).  Contraction into FMAs is
+// off in the schedule, angle and table arithmetic, so every kernel that
+// builds a table (in LDS or ahead of time in global memory) rounds the same
+// way whatever code surrounds it.  Two stages so that a
+// pass can compute the factors while its tile loads are in flight and apply
+// the scale (which may depend on a norm reduction) afterwards.
+__device__ __forceinline__ void table_factors(double2 *fac, int nst, int n, double alpha, double beta) {
+#pragma clang fp contract(off)
+    const int t = threadIdx.x, nt = blockDim.x;
+    for (int j = t; j < nst + 1 + n + 1; j += nt) {
+        double ang = j <= nst ? alpha * (double)(nst - 2 * j) : beta * (double)(n - 2 * (j - nst - 1));
+        double s, c;
+        sincos(ang, &s, &c);
+        fac[j] = make_double2(c, s);
+    }
+}
+
+template <typename Real>
+__device__ __forceinline__ void table_products(Cx<Real> *tab, const double2 *fac, int nst, int n,
+                                               double scale) {
+#pragma clang fp contract(off)
+    const int t = threadIdx.x, nt = blockDim.x;
+    __syncthreads();
+    const int W = n + 1;
+    for (int j = t; j < (nst + 1) * W; j += nt) {
+        const int k = j / W, w = j - k * W;
+        const double2 a = fac[k], b = fac[nst + 1 + w];
+        const double re = (a.x * b.x - a.y * b.y) * scale;
+        const double im = (a.x * b.y + a.y * b.x) * scale;
+        tab[j] = Cx<Real>{(Real)re, (Real)im};
+    }
+    __syncthreads();
+}
+
+template <typename Real>
+__device__ void build_table(Cx<Real> *tab, double2 *fac, int nst, int n, double alpha,
+                            double beta, double scale) {
+    table_factors(fac, nst, n, alpha, beta);
+    table_products<Real>(tab, fac, nst, n, scale);
+}
+
+// Multiply every register element by T[k][w]: elements are visited in
+// Gray-code order so each step updates the syndrome by one uniform column.
+template <typename Real, int R, int PHASE_CHUNK = 0>
+__device__ __forceinline__ void apply_phase(Cx<Real> (&v)[1 << R], const LayCtx<R> &L, int basis,
+                                            int n, const Cx<Real> *tab) {
+    uint32_t s = basis ? L.s0x : L.s0z;
+    const Cx<Real> *tw = tab + L.w0;
+    const int W = n + 1;
+#pragma unroll
+    for (int idx = 0; idx < (1 << R); ++idx) {
+        const int q = idx ^ (idx >> 1);
+        if (idx) s ^= basis ? L.lx[__builtin_ctz(idx)] : L.lz[__builtin_ctz(idx)];
+        v[q] = phase_mul(v[q], tw[__umul24((uint32_t)popc(s), (uint32_t)W) + __builtin_popcount(q)]);
+        // keep the table reads of at most eight elements in flight (register
+        // pressure when a block holds two tiles)
+        if (PHASE_CHUNK && (idx & (PHASE_CHUNK - 1)) == PHASE_CHUNK - 1) __builtin_amdgcn_sched_barrier(0);
+    }
+}
 
 // Sum of |v_q|^2 over a thread's register elements: pairwise in the storage
 // precision (complex64 steps accumulate in FP32), returned as FP64 for the

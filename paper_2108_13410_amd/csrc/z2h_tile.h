@@ -28,6 +28,23 @@ __device__ __forceinline__ Cx<Real> cmul(Cx<Real> a, Cx<Real> b) {
     return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
 }
 
+// Amplitude times phase, the multiply-adds spelled out: kernels that apply
+// one phase in different surroundings round alike.
+__device__ __forceinline__ float madd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double madd(double a, double b, double c) { return __builtin_fma(a, b, c); }
+template <typename Real>
+__device__ __forceinline__ Cx<Real> phase_mul(Cx<Real> a, Cx<Real> b) {
+    return {madd(a.x, b.x, -(a.y * b.y)), madd(a.y, b.x, a.x * b.y)};
+}
+
+// |a|^2 with the product of the imaginary (IM) or the real part inside the
+// multiply-add.  Which one a norm's FP32 sums take shows in their last bits,
+// and with renormalization in the state's.
+template <bool IM, typename Real>
+__device__ __forceinline__ Real abs2(Cx<Real> a) {
+    return IM ? madd(a.y, a.y, a.x * a.x) : madd(a.x, a.x, a.y * a.y);
+}
+
 __device__ __forceinline__ int popc(uint32_t v) { return __builtin_popcount(v); }
 
 // Next 16-byte boundary at or after p (LDS sub-buffers; the host sizes the

@@ -35,9 +35,6 @@ __device__ __forceinline__ double lane_across(double x) {
     return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
 }
 
-__device__ __forceinline__ float madd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double madd(double a, double b, double c) { return __builtin_fma(a, b, c); }
-
 // Exchange of the lane bit of direction B (4 or 5) with the register bit
 // that tells a from b: a keeps its lower lanes and takes b's, b the upper.
 template <int B>
@@ -157,6 +154,98 @@ __device__ __forceinline__ double wave_sum_lanes(double x) {
     x += lane_across<2>(x);
     x += lane_across<1>(x);
     return x + lane_across<0>(x);
+}
+
+// Butterflies over register bits [lo, hi).
+template <int LO, int HI, typename Real, int N>
+__device__ __forceinline__ void reg_layers(Cx<Real> (&v)[N]) {
+#pragma unroll
+    for (int j = LO; j < HI; ++j)
+#pragma unroll
+        for (int q = 0; q < N; ++q)
+            if (!(q & (1 << j))) {
+                const Cx<Real> a = v[q], b = v[q | (1 << j)];
+                v[q] = cadd(a, b);
+                v[q | (1 << j)] = csub(a, b);
+            }
+}
+
+// Exchange of the wave bits with the high WB register bits, through buf.
+// CX: the real, then the imaginary parts, through half the LDS; buf may then
+// be used again after the call without a barrier (else after the next one).
+template <int RB, int WB, bool CX, typename Real>
+__device__ __forceinline__ void wave_exchange(Cx<Real> (&v)[1 << RB], Cx<Real> *buf, uint32_t wave, uint32_t lane) {
+    constexpr int keep = RB - WB;
+    constexpr uint32_t km = (1u << keep) - 1u;
+    auto to = [&](uint32_t q) { return (((wave << RB) | q) << 6) | lane; };
+    auto from = [&](uint32_t q) { return ((((q >> keep) << RB) | (wave << keep) | (q & km)) << 6) | lane; };
+    if constexpr (CX) {
+        Real *b = reinterpret_cast<Real *>(buf);
+#pragma unroll
+        for (uint32_t q = 0; q < (1u << RB); ++q) b[to(q)] = v[q].x;
+        __syncthreads();
+#pragma unroll
+        for (uint32_t q = 0; q < (1u << RB); ++q) v[q].x = b[from(q)];
+        __syncthreads();
+#pragma unroll
+        for (uint32_t q = 0; q < (1u << RB); ++q) b[to(q)] = v[q].y;
+        __syncthreads();
+#pragma unroll
+        for (uint32_t q = 0; q < (1u << RB); ++q) v[q].y = b[from(q)];
+        __syncthreads();
+    } else {
+#pragma unroll
+        for (uint32_t q = 0; q < (1u << RB); ++q) buf[to(q)] = v[q];
+        __syncthreads();
+#pragma unroll
+        for (uint32_t q = 0; q < (1u << RB); ++q) v[q] = buf[from(q)];
+    }
+}
+
+// Transform of a tile of RB + 6 + WB qubits held with lane bits 0-5, wave
+// bits above and register bits on top; it ends in the layout of wave_index.
+// bwd_wave transforms from that layout and ends in the first one.
+template <int RB, int WB, bool CX, typename Real>
+__device__ __forceinline__ void fwd_wave(Cx<Real> (&v)[1 << RB], Cx<Real> *buf, uint32_t wave, uint32_t lane, uint32_t lam) {
+    reg_layers<0, RB>(v);
+    lane_layer<4, true, 0>(v, lam);
+    lane_layer<5, true, 1>(v, lam);
+    if constexpr (WB != 0) {
+        wave_exchange<RB, WB, CX>(v, buf, wave, lane);
+        reg_layers<RB - WB, RB>(v);
+        row_layers<0, 4, true>(v, lam);
+    } else {
+        row_layers<2, 4, true>(v, lam);
+        row_layers<0, 2, true>(v, lam);
+    }
+}
+
+template <int RB, int WB, bool CX, typename Real>
+__device__ __forceinline__ void bwd_wave(Cx<Real> (&v)[1 << RB], Cx<Real> *buf, uint32_t wave, uint32_t lane, uint32_t lam) {
+    // (with fewer than two register bits outside the exchange, lane bit 5 sits
+    // in a wave bit until the exchange back)
+    constexpr bool early5 = WB == 0 || RB - WB >= 2;
+    row_layers<0, 4, false>(v, lam);
+    lane_layer<4, false, 0>(v, lam);
+    if constexpr (early5) lane_layer<5, false, 1>(v, lam);
+    if constexpr (WB != 0) {
+        reg_layers<RB - WB, RB>(v);
+        wave_exchange<RB, WB, CX>(v, buf, wave, lane);
+    }
+    if constexpr (!early5) lane_layer<5, false, 1>(v, lam);
+    reg_layers<0, RB>(v);
+}
+
+// Index of register element q of a thread after fwd_wave.
+template <int RB, int WB>
+__device__ __forceinline__ uint32_t wave_index(uint32_t wave, uint32_t lam, uint32_t q) {
+    constexpr int keep = RB - WB;
+    const uint32_t w = WB ? q >> keep : 0u;                                   // wave bits, in the registers
+    const uint32_t e = WB ? (wave << keep) | (q & ((1u << keep) - 1u)) : q;   // element before the exchange
+    // before it, lane bits 4 and 5 traded places with element bits 0 and 1
+    const uint32_t lo = (lam & 15u) | ((e & 1u) << 4) | ((e & 2u) << 4);
+    const uint32_t el = (e & ~3u) | ((lam >> 4) & 3u);
+    return lo | (w << 6) | (el << (6 + WB));
 }
 
 }  // namespace z2h
