@@ -18,7 +18,8 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           f"--offload-arch={ARCH}"]
 
-SOURCES = ["z2h_kernels.hip", "z2h_resident.hip", "z2h_host.cpp", "z2h_batch.cpp", "z2h_adjoint.cpp", "z2h_tune.cpp", "z2h_path.cpp",
+SOURCES = ["z2h_kernels.hip", "z2h_resident.hip", "z2h_wide.hip", "z2h_host.cpp", "z2h_batch.cpp", "z2h_adjoint.cpp",
+           "z2h_tune.cpp", "z2h_path.cpp",
            "z2h_krylov_kernels.hip", "z2h_krylov.cpp", "z2h_gates.hip", "z2h_circuit.cpp",
            "z2h_noalloc.cpp"]
 
@@ -40,7 +41,8 @@ def _compile(src, verbose):
 # Translation units holding device code (kernels or device variables).  The
 # others are host code only: the planner, launch sequences, batch and path
 # engines, exact-solver host routines and gate-list builders.
-DEVICE_SOURCES = ["z2h_kernels.hip", "z2h_resident.hip", "z2h_resident.hip", "z2h_krylov_kernels.hip", "z2h_gates.hip", "z2h_noalloc.cpp"]
+DEVICE_SOURCES = ["z2h_kernels.hip", "z2h_resident.hip", "z2h_wide.hip", "z2h_krylov_kernels.hip", "z2h_gates.hip",
+                  "z2h_noalloc.cpp"]
 HOST_SOURCES = [s for s in SOURCES if s not in DEVICE_SOURCES]
 SANITIZE_DIR = os.path.join(BUILD, "sanitize")
 SANITIZED_LIB = os.path.join(SANITIZE_DIR, "libz2h.so")

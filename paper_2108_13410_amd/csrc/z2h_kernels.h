@@ -150,11 +150,14 @@ LevelOp level_op_host(int lev, int K, int S, int k0, int order);
 // Register-window shapes (R, NL) with a compiled straight-line kernel.
 bool full_level_ok(int R, int NL);
 bool pair_level_ok(bool c128, int R, int NL);  // two-tile blocks compiled for this shape
+bool wide_level_ok(bool c128, const GroupGeom &g);  // z passes of a wide contiguous group (z2h_wide.hip)
+hipError_t launch_wide(bool c128, const LevelArgs &a, unsigned nblocks, hipStream_t s);
 bool cx_level_ok(int R, int NL);               // component-exchange kernels compiled for this shape
 
 // Set the dynamic-LDS limit of every kernel (call before graph capture).
 hipError_t prepare_kernels();
 hipError_t prepare_resident();
+hipError_t prepare_wide();
 hipError_t set_lds(const void *fn, size_t lds);  // of one kernel, to the largest block any plan uses
 
 }  // namespace z2h

@@ -1305,11 +1305,15 @@ hipError_t prepare_kernels() {
     if (e == hipSuccess) e = prep_real<float>();
     if (e == hipSuccess) e = prep_real<double>();
     if (e == hipSuccess) e = prepare_resident();
+    if (e == hipSuccess) e = prepare_wide();
     return e;
 }
 
 hipError_t launch_level(bool c128, int R, const LevelArgs &a, unsigned nblocks, size_t lds,
                         hipStream_t s) {
+    // every job of the launch has a phase pass: the wide group's own kernel
+    // (other kinds, and launches that mix them, run in the general one)
+    if (a.kind_hint == kPhaseB && a.group == 0 && wide_level_ok(c128, a.geom)) return launch_wide(c128, a, nblocks, s);
     Z2H_DISPATCH(do_level, a, dim3(nblocks), lds, s);
 }
 
