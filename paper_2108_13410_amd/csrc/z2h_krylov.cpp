@@ -29,6 +29,13 @@ int ham_workers(const GroupGeom &g) {
     return (int)std::min<uint64_t>(tiles, (uint64_t)kHamWorkersMax);
 }
 
+// Groups of qubits a Hamiltonian pass is made for, and the workgroups (one
+// partial each) of the passes over a group.
+int ham_groups(const Plan &P) { return ham_wide_ok(P.c128, P.n) ? 2 : P.K; }
+int ham_workers(const Plan &P, int group) {
+    return ham_wide_ok(P.c128, P.n) ? kHamWideWorkers : ham_workers(P.geom[group]);
+}
+
 unsigned vec_blocks(const Plan &P) {
     const uint64_t need = ((1ull << P.n) + 255) / 256;
     return (unsigned)std::min<uint64_t>(need, (uint64_t)kVecBlocks);
@@ -38,6 +45,15 @@ unsigned vec_blocks(const Plan &P) {
 // grids of eight or more workers per CU (as the Trotter pass kernels).
 static int ham_xcd(const Plan &P, int group, int workers) {
     return ((P.xcd >> group) & 1) && workers >= 8 * 256 ? 1 : 0;
+}
+
+// Pass i, over group gi.
+hipError_t launch_pass(const Plan &P, HamArgs &a, int gi, int i, hipStream_t s) {
+    if (ham_wide_ok(P.c128, P.n)) return launch_ham_wide(i < 2 ? i : !a.lz ? 3 : a.g ? 4 : 2, a, s);
+    const int w = ham_workers(P, gi);
+    a.geom = P.geom[gi];
+    a.xcd = ham_xcd(P, gi, w);
+    return launch_ham(P.c128, a.geom.R, a, (unsigned)w, obs_lds_bytes(P, a.geom, a.geom.R), s);
 }
 
 // y = H x: passes over groups 0, 1, .., K-1, .., 1, 0 (one pass when K = 1).
@@ -52,20 +68,17 @@ z2h_status ham_passes(const Plan &P, const void *x, void *y, const z2h_couplings
     a.hx = H.hx;
     a.hz = H.hz;
     a.xscale = std::ldexp(1.0, -P.n);
-    const int K = P.K, npass = 2 * K - 1;
+    const int K = ham_groups(P), npass = 2 * K - 1;
     for (int i = 0; i < npass; ++i) {
         const int gi = i < K ? i : 2 * K - 2 - i;
-        a.geom = P.geom[gi];
         a.src = i == 0 ? x : y;
         a.dst = y;
         a.top = gi == K - 1;
         a.final_pass = i == npass - 1;
         a.x = a.final_pass ? x : nullptr;
         a.part = a.final_pass ? apart : nullptr;
-        const int w = ham_workers(a.geom);
-        a.xcd = ham_xcd(P, gi, w);
-        if (a.final_pass && napart) *napart = w;
-        hipError_t e = launch_ham(P.c128, a.geom.R, a, (unsigned)w, obs_lds_bytes(P, a.geom, a.geom.R), s);
+        if (a.final_pass && napart) *napart = ham_workers(P, gi);
+        hipError_t e = launch_pass(P, a, gi, i, s);
         if (e != hipSuccess) return fail(Z2H_ERR_HIP, "Hamiltonian pass failed: %s", hipGetErrorString(e));
     }
     return Z2H_OK;
@@ -113,14 +126,14 @@ z2h_status norm_start(const Plan &P, const void *u, const LanczosWs &L, hipStrea
     return Z2H_OK;
 }
 
-z2h_status launch_scalar_k(const LanczosWs &L, int k, int napart, int napart2, int nwpart, hipStream_t s) {
+z2h_status launch_scalar_k(const LanczosWs &L, const double *wpart, int k, int napart, int napart2, int nwpart, hipStream_t s) {
     ScalarArgs sa;
     memset(&sa, 0, sizeof sa);
     sa.apart = L.apart;
     sa.napart = napart;
     sa.apart2 = napart2 ? L.apart_x : nullptr;
     sa.napart2 = napart2;
-    sa.wpart = L.wpart;
+    sa.wpart = wpart;
     sa.nwpart = nwpart;
     sa.k = k;
     sa.mode = 0;
@@ -130,14 +143,28 @@ z2h_status launch_scalar_k(const LanczosWs &L, int k, int napart, int napart2, i
     return Z2H_OK;
 }
 
+// Iterations whose last pass takes the coefficients from the partials
+// themselves: the |w|^2 partials of two iterations fit the vector-kernel
+// slots side by side (one half is read while the other is written).
+bool coefs_inline(const Plan &P) { return ham_groups(P) > 1 && ham_workers(P, 0) <= kVecBlocks / 2; }
+
 // One Lanczos iteration k: w = sigma_k (H u - alpha_k u) - beta_k sigma_{k-1} p
-// written to w; coef[k].alpha and coef[k+1] (beta, sigma).  With several
+// written to w; coef[k].alpha and coef[k+1] (beta, sigma), the latter by the
+// next iteration, or now if last.  With several
 // groups the update is fused into the Hamiltonian's passes (alpha from the
 // first and the top pass, w written by the last one); a one-group plan
 // forms y = H u and updates in an elementwise kernel.
+// acc (wide passes, k > 0): the Ritz vector takes u and p on the way.
+struct RitzAcc {
+    void *g;
+    double sp, su;
+    int first;
+};
 z2h_status lanczos_iter(const Plan &P, const z2h_couplings &H, int k, const void *u, const void *p, void *w,
-                        void *y, const LanczosWs &L, hipStream_t s) {
-    if (P.K > 1) {
+                        void *y, const LanczosWs &L, bool last, hipStream_t s, const RitzAcc *acc = nullptr) {
+    if (ham_groups(P) > 1) {
+        const bool inl = coefs_inline(P);
+        double *wpart = L.wpart + (inl && (k & 1) ? kVecBlocks / 2 : 0);
         HamArgs a;
         memset(&a, 0, sizeof a);
         a.lat = P.lat;
@@ -146,11 +173,10 @@ z2h_status lanczos_iter(const Plan &P, const z2h_couplings &H, int k, const void
         a.hx = H.hx;
         a.hz = H.hz;
         a.xscale = std::ldexp(1.0, -P.n);
-        const int K = P.K, npass = 2 * K - 1;
-        const int nz = ham_workers(P.geom[0]), nx = ham_workers(P.geom[K - 1]);
+        const int K = ham_groups(P), npass = 2 * K - 1;
+        const int nz = ham_workers(P, 0), nx = ham_workers(P, K - 1);
         for (int i = 0; i < npass; ++i) {
             const int gi = i < K ? i : 2 * K - 2 - i;
-            a.geom = P.geom[gi];
             a.src = i == 0 ? u : y;
             a.dst = y;
             a.top = gi == K - 1;
@@ -163,20 +189,29 @@ z2h_status lanczos_iter(const Plan &P, const z2h_couplings &H, int k, const void
                 a.p = k > 0 ? p : nullptr;
                 a.use_prev = k > 0;
                 a.w = w;
-                a.part_w = L.wpart;
+                a.part_w = wpart;
+                a.record = inl;
+                if (inl && k > 0) {
+                    a.prev_w = L.wpart + (k & 1 ? 0 : kVecBlocks / 2);
+                    a.nprev_w = nz;
+                }
                 a.apart_z = L.apart;
                 a.napart_z = nz;
                 a.apart_x = L.apart_x;
                 a.napart_x = nx;
                 a.coef = L.coef;
                 a.k = k;
+                if (acc) {
+                    a.g = acc->g;
+                    a.g_first = acc->first;
+                    a.gs[0] = acc->sp;
+                    a.gs[1] = acc->su;
+                }
             }
-            a.xcd = ham_xcd(P, gi, ham_workers(a.geom));
-            hipError_t e = launch_ham(P.c128, a.geom.R, a, (unsigned)ham_workers(a.geom),
-                                      obs_lds_bytes(P, a.geom, a.geom.R), s);
+            hipError_t e = launch_pass(P, a, gi, i, s);
             if (e != hipSuccess) return fail(Z2H_ERR_HIP, "Lanczos pass failed: %s", hipGetErrorString(e));
         }
-        return launch_scalar_k(L, k, nz, nx, nz, s);
+        return inl && !last ? Z2H_OK : launch_scalar_k(L, wpart, k, nz, nx, nz, s);
     }
     int napart = 0;
     z2h_status st = ham_passes(P, u, y, H, L.apart, &napart, s);
@@ -198,7 +233,7 @@ z2h_status lanczos_iter(const Plan &P, const z2h_couplings &H, int k, const void
     const unsigned nb = vec_blocks(P);
     hipError_t e = launch_vec(P.c128, v, nb, s);
     if (e != hipSuccess) return fail(Z2H_ERR_HIP, "Lanczos update failed: %s", hipGetErrorString(e));
-    return launch_scalar_k(L, k, napart, 0, (int)nb, s);
+    return launch_scalar_k(L, L.wpart, k, napart, 0, (int)nb, s);
 }
 
 // Both pointers valid and the byte ranges [a, a + na) and [b, b + nb) disjoint.
@@ -422,10 +457,11 @@ z2h_status z2h_lanczos_ground(const z2h_plan *plan, void *d_v, void *d_ws, size_
         double theta = 0.0, prev = NAN;
         int done = 0;
         for (int k = 0; k < max_iter; ++k) {
-            if ((st = lanczos_iter(P, *H, k, u, p, p, y, L, s))) return st;
-            std::swap(u, p);  // the new vector was written over the previous one
             done = k + 1;
-            if (done % kCheckEvery != 0 && done != max_iter) continue;
+            const bool check = done % kCheckEvery == 0 || done == max_iter;
+            if ((st = lanczos_iter(P, *H, k, u, p, p, y, L, check, s))) return st;
+            std::swap(u, p);  // the new vector was written over the previous one
+            if (!check) continue;
             HIP_TRY(hipMemcpyAsync(hc.data(), L.coef, sizeof(LanczosCoef) * (size_t)(done + 1), hipMemcpyDeviceToHost, s));
             HIP_TRY(hipStreamSynchronize(s));
             if (!(hc[0].beta > 0.0)) return fail(Z2H_ERR_NUMERIC, "start vector has zero norm");
@@ -512,7 +548,7 @@ z2h_status z2h_exact_evolve(const z2h_plan *plan, void *d_state, void *d_ws, siz
             if (!finite4(H)) return fail(Z2H_ERR_INVALID, "step %lld: couplings not finite", (long long)k);
             if ((st = norm_start(P, d_state, L, s))) return st;
             for (int j = 0; j < m; ++j) {
-                if ((st = lanczos_iter(P, H, j, ub[j], j > 0 ? ub[j - 1] : nullptr, (void *)ub[j + 1], y, L, s)))
+                if ((st = lanczos_iter(P, H, j, ub[j], j > 0 ? ub[j - 1] : nullptr, (void *)ub[j + 1], y, L, j + 1 == m, s)))
                     return st;
             }
             HIP_TRY(hipMemcpyAsync(hc.data(), L.coef, sizeof(LanczosCoef) * (size_t)(m + 1), hipMemcpyDeviceToHost, s));
@@ -585,23 +621,33 @@ z2h_status z2h_lanczos_vector(const z2h_plan *plan, void *d_v, void *d_ws, size_
         lanczos_carve(P, 3, iters + 2, (char *)d_ws, &L);
         void *u = d_v, *p = L.vec[0], *y = L.vec[1], *g = L.vec[2];
         // the same recurrence again (same kernels, so the same vectors),
-        // accumulating g = sum_k s_k v_k
+        // accumulating g = sum_k s_k v_k, two vectors at a time; where the
+        // update's pass reads both anyway (wide passes), inside it
+        auto fused = [&](int k) { return ham_wide_ok(P.c128, P.n) && (k & 1) && k + 1 < iters; };
         if ((st = norm_start(P, u, L, s))) return st;
         const unsigned nb = vec_blocks(P);
         for (int k = 0; k < iters; ++k) {
-            AccArgs a;
-            memset(&a, 0, sizeof a);
-            a.g = g;
-            a.u = u;
-            a.coef = L.coef;
-            a.s = sv[k];
-            a.k = k;
-            a.first = k == 0;
-            a.nelem = 1ull << P.n;
-            hipError_t e = launch_acc(P.c128, a, nb, s);
-            if (e != hipSuccess) return fail(Z2H_ERR_HIP, "Ritz accumulation failed: %s", hipGetErrorString(e));
+            if (!fused(k) && ((k & 1) || k + 1 == iters)) {
+                AccArgs a;
+                memset(&a, 0, sizeof a);
+                const int k0 = k & ~1;
+                a.g = g;
+                a.u = k & 1 ? p : u;
+                a.u2 = k & 1 ? u : nullptr;
+                a.coef = L.coef;
+                a.s = sv[k0];
+                a.s2 = k & 1 ? sv[k] : 0.0;
+                a.k = k0;
+                a.first = k0 == 0;
+                a.nelem = 1ull << P.n;
+                hipError_t e = launch_acc(P.c128, a, nb, s);
+                if (e != hipSuccess) return fail(Z2H_ERR_HIP, "Ritz accumulation failed: %s", hipGetErrorString(e));
+            }
             if (k + 1 < iters) {
-                if ((st = lanczos_iter(P, *H, k, u, p, p, y, L, s))) return st;
+                // (an accumulation launch for k + 1 reads that vector's coefficient)
+                const bool last = !fused(k + 1) && (((k + 1) & 1) || k + 2 == iters);
+                const RitzAcc acc{g, k ? sv[k - 1] : 0.0, sv[k], k == 1};
+                if ((st = lanczos_iter(P, *H, k, u, p, p, y, L, last, s, fused(k) ? &acc : nullptr))) return st;
                 std::swap(u, p);
             }
         }

@@ -22,6 +22,7 @@
 #include "z2h_kernels.h"
 #include "z2h_solvers.h"
 #include "z2h_tile.h"
+#include "z2h_wave.h"
 
 namespace z2h {
 
@@ -33,8 +34,9 @@ __device__ __forceinline__ double diag_value(int nst, int n, uint32_t s, int w, 
 // v *= scale * D_X for the register elements of layout L (Hadamard basis);
 // accx (if not null) accumulates scale * sum D_X |v|^2 of the values before
 // (a pointer: the accumulator then lives in a scratch slot rather than in
-// one of the registers the two prefetched tiles need).
-template <typename Real, int R>
+// one of the registers the two prefetched tiles need).  At most C elements'
+// diagonals are live at a time.
+template <typename Real, int R, int C = 1 << R>
 __device__ __forceinline__ void mul_diag_x(Cx<Real> (&v)[1 << R], const LayCtx<R> &L, const LatticeDev &lat,
                                            double J, double h, double scale, double *accx) {
     uint32_t s = L.s0x;
@@ -47,6 +49,8 @@ __device__ __forceinline__ void mul_diag_x(Cx<Real> (&v)[1 << R], const LayCtx<R
         const Real d = (Real)dd;
         v[q].x *= d;
         v[q].y *= d;
+        if constexpr (C < (1 << R))
+            if (idx % C == C - 1) __builtin_amdgcn_sched_barrier(0);
     }
 }
 
@@ -139,6 +143,46 @@ __device__ __forceinline__ void lanczos_out(const Cx<Real> (&v)[1 << R], const C
     }
 }
 
+// A value that every lane of the block holds alike, moved to scalar registers.
+__device__ __forceinline__ double uniform(double x) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+    return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
+}
+
+// Lanczos coefficients of this iteration: sigma_k, alpha_k and
+// cp = beta_k sigma_{k-1}.  Every block sums the partials of the first and
+// the top pass itself, and, where prev_w is given, beta_k and sigma_k from
+// the last iteration's |w|^2 partials; block 0 then records them (a launch of
+// one block between two iterations took 4 us, 10 us for 2048 partials).
+__device__ __forceinline__ void lanczos_coefs(const HamArgs &a, double *red, double &sig, double &alpha, double &cp) {
+    const int t = (int)threadIdx.x, nt = (int)blockDim.x;
+    double sm = 0.0;
+    for (int j = t; j < a.napart_z; j += nt) sm += a.apart_z[j];
+    for (int j = t; j < a.napart_x; j += nt) sm += a.apart_x[j];
+    double beta;
+    if (a.prev_w) {
+        double sw = 0.0;
+        for (int j = t; j < a.nprev_w; j += nt) sw += a.prev_w[j];
+        beta = uniform(sqrt(block_sum(sw, red)));
+        sig = beta > 1e-300 ? 1.0 / beta : 0.0;
+    } else {
+        beta = a.coef[a.k].beta;
+        sig = a.coef[a.k].sigma;
+    }
+    sig = uniform(sig);
+    alpha = uniform(sig * sig * block_sum(sm, red));
+    cp = a.use_prev ? beta * a.coef[a.k - 1].sigma : 0.0;
+    if (a.record && blockIdx.x == 0 && t == 0) {
+        a.coef[a.k].alpha = alpha;
+        if (a.prev_w) {  // (else they are there, and other blocks read them)
+            a.coef[a.k].beta = beta;
+            a.coef[a.k].sigma = sig;
+        }
+    }
+}
+
 // PF: the next tile's elements are loaded while the current one is
 // transformed (two register tiles; used where they fit without spilling).
 template <typename Real, int R, bool PF, bool SP>
@@ -156,18 +200,8 @@ __global__ void __launch_bounds__(512) ham_kernel(HamArgs a) {
     const bool lz = a.lz && a.final_pass;
     double acc = 0.0, accz = 0.0, accx = 0.0;
 
-    // Lanczos coefficients of this iteration (every block sums the partials
-    // of the first and the top pass itself)
     double sig = 0.0, alpha = 0.0, cp = 0.0;
-    if (lz) {
-        const LanczosCoef ck = a.coef[a.k];
-        sig = ck.sigma;
-        double sm = 0.0;
-        for (int j = (int)t; j < a.napart_z; j += (int)blockDim.x) sm += a.apart_z[j];
-        for (int j = (int)t; j < a.napart_x; j += (int)blockDim.x) sm += a.apart_x[j];
-        alpha = sig * sig * block_sum(sm, red);
-        cp = a.use_prev ? ck.beta * a.coef[a.k - 1].sigma : 0.0;
-    }
+    if (lz) lanczos_coefs(a, red, sig, alpha, cp);
 
     const bool syn0 = a.final_pass || a.part_z;
     // logical block: first tile of the grid-stride walk and partial slot
@@ -177,7 +211,7 @@ __global__ void __launch_bounds__(512) ham_kernel(HamArgs a) {
     LayCtx<R> Ln;
     if constexpr (PF) {
         if (tile < tiles) {
-            lay_ctx<R, SP>(Ln, g, a.lat, tile, g.p[0], t, syn0);
+            lay_ctx<R, SP>(Ln, g, a.lat, tile, g.p[0], t, syn0, 0);
             load_tile<Real, R, false, SP>(vn, src, Ln);
         }
     }
@@ -190,11 +224,11 @@ __global__ void __launch_bounds__(512) ham_kernel(HamArgs a) {
             for (int q = 0; q < (1 << R); ++q) v[q] = vn[q];
             const uint64_t nt = tile + gridDim.x;
             if (nt < tiles) {
-                lay_ctx<R, SP>(Ln, g, a.lat, nt, g.p[0], t, syn0);
+                lay_ctx<R, SP>(Ln, g, a.lat, nt, g.p[0], t, syn0, 0);
                 load_tile<Real, R, false, SP>(vn, src, Ln);
             }
         } else {
-            lay_ctx<R, SP>(L0, g, a.lat, tile, g.p[0], t, syn0);
+            lay_ctx<R, SP>(L0, g, a.lat, tile, g.p[0], t, syn0, 0);
             load_tile<Real, R, false, SP>(v, src, L0);
         }
         if (a.part_z) accz += diag_norm_z<Real, R>(v, L0, a.lat, a.JB, a.hz);
@@ -206,7 +240,7 @@ __global__ void __launch_bounds__(512) ham_kernel(HamArgs a) {
         }
         if (a.top) {
             LayCtx<R> Lm;
-            lay_ctx<R, SP>(Lm, g, a.lat, tile, g.p[cur], t, true);
+            lay_ctx<R, SP>(Lm, g, a.lat, tile, g.p[cur], t, true, 1);
             mul_diag_x<Real, R>(v, Lm, a.lat, a.JA, a.hx, a.xscale, a.part_x ? &accx : nullptr);
             for (int j = g.nlay - 1; j >= 0; --j) {
                 if (j != cur) {
@@ -240,6 +274,152 @@ __global__ void __launch_bounds__(512) ham_kernel(HamArgs a) {
     if (a.part_x) {
         const double s = block_sum(accx, red);
         if (t == 0) a.part_x[lb] = s;
+    }
+}
+
+// Passes of y = H x over a 24-qubit complex128 state in two groups, the 13
+// low qubits and the 11 high ones: three passes where narrower groups take
+// five (ROLE 0 the low group forward, 1 the high group with the X-basis
+// diagonal, 2 and 3 the low group's way back with the Lanczos update or with
+// D_Z x added; 4 is 2 with the Ritz vector's sum of the two vectors it reads).  A tile of 2^13 elements is 128 KiB.  In ham_kernel it fills
+// the LDS: one workgroup per CU, four layout changes a pass, and three such
+// passes take as long as five of 2^12.  Here six bits are transformed in the
+// wave and the three wave bits through half of that LDS, one component at a
+// time, so two workgroups share a CU; the state between two passes stays in
+// the order the transform leaves it in (the same addresses), with the signs
+// that lane_layer defers.
+//
+// Two blocks per CU walk the tiles, so the coefficients are summed from 512
+// partials once for four tiles.  Tiles of the high group hold 64-byte runs;
+// neighbours meet in one XCD's L2.
+//
+// At 256 MiB a pass takes 101 us (5.3 TB/s; a large copy 4.6, in place 5.9),
+// 110 us (158 without the row mixing below), 212 us for the update's four
+// streams and 318 us for six; a Lanczos iteration 649 -> 433 us, and 2 x 134
+// us less of separate accumulation per two vectors for 106 us more here.
+// Two elements of each operand at a time in the update: with four the
+// registers spill (role 4: 406 us).
+template <int ROLE>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) ham_wide_kernel(HamArgs a) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    constexpr int RB = 4, WB = 3, M = RB + 6 + WB, C = 2 * M - kHamWideQubits;
+    constexpr bool high = ROLE == 1, lanczos = ROLE == 2 || ROLE == 4;
+    using V = Cx<double>;
+    V *lds = reinterpret_cast<V *>(smem);  // one component of the tile
+    double *red = reinterpret_cast<double *>(smem + (sizeof(double) << M));
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, lam = wave_lane(lane);
+    const V *src = reinterpret_cast<const V *>(a.src), *x = reinterpret_cast<const V *>(a.x);
+    V *dst = reinterpret_cast<V *>(a.dst);
+    const uint32_t lb = xcd_major(blockIdx.x, gridDim.x);
+    double acc = 0.0, sig = 0.0, alpha = 0.0, cp = 0.0;
+    if constexpr (lanczos) lanczos_coefs(a, red, sig, alpha, cp);
+    const double g0 = ROLE == 4 ? a.gs[0] * a.coef[a.k - 1].sigma : 0.0, g1 = a.gs[1] * sig;
+    // Tile index of the thread's element q: nat(q) | nat_t as the transform
+    // starts, fin(q) | fin_t as it ends; at() maps it to the state's (the
+    // high group's tile holds 2^C neighbours of each of its 2^11 elements).
+    // The q part of an address is uniform, the thread's byte offset fits 32
+    // bits.
+    const uint32_t nat_t = (wave << 6) | lam, fin_t = wave_index<RB, WB>(wave, lam, 0u);
+    auto at = [](uint32_t i) -> uint32_t { return high ? (i & ((1u << C) - 1u)) | ((i >> C) << M) : i; };
+    auto nat = [&](uint32_t q) { return at(q << (6 + WB)); };
+    auto fin = [&](uint32_t q) { return at(wave_index<RB, WB>(0u, 0u, q)); };
+    constexpr uint32_t row = (1u << M) - 1u, nat_q = row & ~((1u << (6 + WB - C + 3)) - 1u);
+    constexpr uint32_t fin_q = wave_index<RB, WB>(0u, 0u, (1u << RB) - 1u);
+    for (uint32_t tile = lb; tile < 1u << (kHamWideQubits - M); tile += gridDim.x) {
+        const uint32_t t0 = high ? tile << C : tile << M;
+        auto elem = [&](const V *b, uint32_t u, uint32_t off) -> const V & {
+            return *reinterpret_cast<const V *>(reinterpret_cast<const char *>(b + u) + off);
+        };
+        // Between the passes the element of the high index h and the low
+        // index l sits at l ^ (h << 3): the high group's rows, 128 KiB apart,
+        // then start in different memory channels.
+        auto mix = [](uint32_t h) { return (h << 3) & row; };
+        auto y_q = [&](uint32_t q) -> uint32_t {
+            return high ? nat(q) | ((t0 ^ mix((q << (6 + WB)) >> C)) & nat_q) : t0 | (fin(q) ^ (mix(tile) & fin_q));
+        };
+        const uint32_t y_t = high ? at(nat_t & ~((1u << C) - 1u)) | (((t0 ^ mix(nat_t >> C)) & (row & ~nat_q)) | (nat_t & ((1u << C) - 1u)))
+                                  : fin_t ^ (mix(tile) & ~fin_q);
+        const uint32_t nat_b = nat_t * (uint32_t)sizeof(V), y_b = y_t * (uint32_t)sizeof(V);
+        V v[1 << RB];
+#pragma unroll
+        for (uint32_t q = 0; q < (1u << RB); ++q) v[q] = ROLE == 0 ? elem(src, t0 | nat(q), nat_b) : elem(src, y_q(q), y_b);
+        LayCtx<RB> L;
+        const uint32_t i0 = t0 | at(high ? fin_t : nat_t);
+        L.w0 = popc(i0);
+        if constexpr (high) {
+            L.s0x = syndrome_direct(a.lat.xmask, i0);
+#pragma unroll
+            for (int r = 0; r < RB; ++r) L.lx[r] = a.lat.xsyn[wave_reg_bit<RB, WB>(r) - C + M];
+            fwd_wave<RB, WB, true, C>(v, lds, wave, lane, lam);
+            mul_diag_x<double, RB, 4>(v, L, a.lat, a.JA, a.hx, a.xscale, &acc);
+            bwd_wave<RB, WB, true, C>(v, lds, wave, lane, lam);
+        } else {
+            L.s0z = syndrome_direct(a.lat.zmask, i0);
+#pragma unroll
+            for (int r = 0; r < RB; ++r) L.lz[r] = a.lat.zsyn[6 + WB + r];
+            if constexpr (ROLE == 0) {
+                if (a.part_z) acc += diag_norm_z<double, RB>(v, L, a.lat, a.JB, a.hz);
+                fwd_wave<RB, WB, true>(v, lds, wave, lane, lam);
+            } else {
+                bwd_wave<RB, WB, true>(v, lds, wave, lane, lam);
+            }
+        }
+        uint32_t ob = ROLE < 2 ? y_b : nat_b;
+        asm volatile("" : "+v"(ob));  // (addresses are formed again, not kept)
+        if constexpr (ROLE < 2) {
+#pragma unroll
+            for (uint32_t q = 0; q < (1u << RB); ++q) const_cast<V &>(elem(dst, y_q(q), ob)) = v[q];
+        } else {
+            // + D_Z x, CH elements of each operand at a time
+            const V *p = reinterpret_cast<const V *>(a.use_prev ? a.p : a.x);  // (cp = 0 without one)
+            V *w = lanczos ? reinterpret_cast<V *>(a.w) : dst;
+            V *gout = reinterpret_cast<V *>(a.g);
+            const V *g = a.g_first ? x : gout;  // (gf = 0 then)
+            const double gf = a.g_first ? 0.0 : 1.0;
+            constexpr uint32_t CH = 2;
+            uint32_t s = L.s0z;
+#pragma unroll
+            for (uint32_t c0 = 0; c0 < (1u << RB); c0 += CH) {
+                V xv[CH], pv[CH];
+#pragma unroll
+                for (uint32_t i = 0; i < CH; ++i) {
+                    const uint32_t q = (c0 + i) ^ ((c0 + i) >> 1);
+                    xv[i] = elem(x, t0 | nat(q), ob);
+                    if constexpr (lanczos) pv[i] = elem(p, t0 | nat(q), ob);
+                }
+#pragma unroll
+                for (uint32_t i = 0; i < CH; ++i) {
+                    const uint32_t idx = c0 + i, q = idx ^ (idx >> 1);
+                    if (idx) s ^= L.lz[__builtin_ctz(idx)];
+                    const double d = diag_value(a.lat.nst, a.lat.n, s, L.w0 + popc(q), a.JB, a.hz);
+                    V r{v[q].x + (d - alpha) * xv[i].x, v[q].y + (d - alpha) * xv[i].y};
+                    if constexpr (lanczos) {
+                        r = V{sig * r.x - cp * pv[i].x, sig * r.y - cp * pv[i].y};
+                        acc += r.x * r.x + r.y * r.y;
+                    } else {
+                        acc += xv[i].x * r.x + xv[i].y * r.y;
+                    }
+                    const_cast<V &>(elem(w, t0 | nat(q), ob)) = r;
+                }
+                if constexpr (ROLE == 4) {
+                    V gv[CH];
+#pragma unroll
+                    for (uint32_t i = 0; i < CH; ++i) gv[i] = elem(g, t0 | nat((c0 + i) ^ ((c0 + i) >> 1)), ob);
+#pragma unroll
+                    for (uint32_t i = 0; i < CH; ++i) {
+                        const V o{gf * gv[i].x + g0 * pv[i].x, gf * gv[i].y + g0 * pv[i].y};
+                        const_cast<V &>(elem(gout, t0 | nat((c0 + i) ^ ((c0 + i) >> 1)), ob)) =
+                            V{o.x + g1 * xv[i].x, o.y + g1 * xv[i].y};
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+    double *part = ROLE == 0 ? a.part_z : ROLE == 1 ? a.part_x : lanczos ? a.part_w : a.part;
+    if (part) {
+        const double s = block_sum(acc, red);
+        if (threadIdx.x == 0) part[lb] = s;
     }
 }
 
@@ -325,7 +505,9 @@ template <typename Real>
 __global__ void __launch_bounds__(256) acc_kernel(AccArgs a) {
     Cx<Real> *g = reinterpret_cast<Cx<Real> *>(a.g);
     const Cx<Real> *u = reinterpret_cast<const Cx<Real> *>(a.u);
+    const Cx<Real> *u2 = reinterpret_cast<const Cx<Real> *>(a.u2);
     const double c = a.s * a.coef[a.k].sigma;
+    const double c2 = u2 ? a.s2 * a.coef[a.k + 1].sigma : 0.0;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.nelem; i += stride) {
         const Cx<Real> e = u[i];
@@ -334,6 +516,11 @@ __global__ void __launch_bounds__(256) acc_kernel(AccArgs a) {
             const Cx<Real> o = g[i];
             re += (double)o.x;
             im += (double)o.y;
+        }
+        if (u2) {  // (rounded in between, as two launches would)
+            const Cx<Real> f = u2[i];
+            re = c2 * (double)f.x + (double)(Real)re;
+            im = c2 * (double)f.y + (double)(Real)im;
         }
         g[i] = Cx<Real>{(Real)re, (Real)im};
     }
@@ -414,6 +601,30 @@ hipError_t launch_ham(bool c128, int R, const HamArgs &a, unsigned workers, size
             case 4: return do_ham<float, 4>(a, workers, lds, s);
             case 5: return do_ham<float, 5>(a, workers, lds, s);
         }
+    }
+    return hipErrorInvalidValue;
+}
+
+bool ham_wide_ok(bool c128, int n) { return c128 && n == kHamWideQubits; }
+
+template <int ROLE>
+static hipError_t do_ham_wide(const HamArgs &a, hipStream_t s) {
+    constexpr size_t lds = (sizeof(double) << 13) + 16 * sizeof(double);
+    const void *fn = reinterpret_cast<const void *>(&ham_wide_kernel<ROLE>);
+    hipError_t e = allow_lds(fn, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(ham_wide_kernel<ROLE>, dim3(kHamWideWorkers), dim3(512), lds, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_ham_wide(int role, const HamArgs &a, hipStream_t s) {
+    if (!ham_wide_ok(true, a.lat.n)) return hipErrorInvalidValue;
+    switch (role) {
+        case 0: return do_ham_wide<0>(a, s);
+        case 1: return do_ham_wide<1>(a, s);
+        case 2: return do_ham_wide<2>(a, s);
+        case 3: return do_ham_wide<3>(a, s);
+        case 4: return do_ham_wide<4>(a, s);
     }
     return hipErrorInvalidValue;
 }

@@ -41,9 +41,14 @@ struct HamArgs {
     void *w;                   // Lanczos final pass: output (may equal p)
     double *part_w;            // Lanczos final pass: |w|^2 partials
     const double *apart_z, *apart_x;
-    const LanczosCoef *coef;
-    int32_t napart_z, napart_x;
+    const double *prev_w;      // |w|^2 partials of the iteration before, or null: coef[k] holds beta and sigma
+    LanczosCoef *coef;
+    int32_t napart_z, napart_x, nprev_w;
+    int32_t record;            // 1: the last pass writes coef[k] (nothing follows that would)
     int32_t k, use_prev, lz;
+    int32_t g_first;           // 1: g is written, not added to
+    void *g;                   // Ritz vector, or null: g += gs[0] sigma_{k-1} p + gs[1] sigma_k x (wide passes)
+    double gs[2];
     GroupGeom geom;
     LatticeDev lat;
     int32_t top;               // 1: transform, X-basis diagonal, transform back
@@ -51,7 +56,6 @@ struct HamArgs {
     double JA, JB, hx, hz;
     double xscale;             // 2^-n: the two unnormalised transforms
     int32_t xcd;               // 1: XCD-major block order (partials indexed by logical block)
-    int32_t pad;
 };
 
 // w = sigma_k (y - alpha_k u) - beta_k sigma_{k-1} p (elementwise; w may equal p)
@@ -90,12 +94,14 @@ struct CombineArgs {
     uint64_t nelem;
 };
 
-// Ritz-vector accumulation: g = (first ? 0 : g) + s * coef[k].sigma * u.
+// Ritz-vector accumulation: g = (first ? 0 : g) + s * coef[k].sigma * u
+// (+ s2 * coef[k + 1].sigma * u2 if u2 is not null: two vectors in one pass
+// read and write g once: 2 x 134 -> 200 us at 24 qubits, complex128).
 struct AccArgs {
     void *g;
-    const void *u;
+    const void *u, *u2;
     const LanczosCoef *coef;
-    double s;
+    double s, s2;
     int32_t k, first;
     uint64_t nelem;
 };
@@ -112,8 +118,15 @@ struct DotArgs {
 
 constexpr int kVecBlocks = 2048;   // blocks of the elementwise Lanczos kernels
 constexpr int kHamWorkersMax = 2048;
+// Complex128 states of this size run the Hamiltonian in two groups of qubits
+// by kernels of their own, whatever the plan's groups (two tiles of 2^13
+// cover them with 64-byte runs); other sizes in the plan's.
+constexpr int kHamWideQubits = 24;
+constexpr int kHamWideWorkers = 512;   // two per CU
 
 hipError_t launch_ham(bool c128, int R, const HamArgs &a, unsigned workers, size_t lds, hipStream_t s);
+bool ham_wide_ok(bool c128, int n);
+hipError_t launch_ham_wide(int role, const HamArgs &a, hipStream_t s);   // (roles: see the kernel)
 hipError_t launch_vec(bool c128, const VecArgs &a, unsigned blocks, hipStream_t s);
 hipError_t launch_scalar(const ScalarArgs &a, hipStream_t s);
 hipError_t launch_combine(bool c128, const CombineArgs &a, unsigned blocks, hipStream_t s);

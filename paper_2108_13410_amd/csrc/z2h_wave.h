@@ -204,28 +204,30 @@ __device__ __forceinline__ void wave_exchange(Cx<Real> (&v)[1 << RB], Cx<Real> *
 
 // Transform of a tile of RB + 6 + WB qubits held with lane bits 0-5, wave
 // bits above and register bits on top; it ends in the layout of wave_index.
-// bwd_wave transforms from that layout and ends in the first one.
-template <int RB, int WB, bool CX, typename Real>
+// bwd_wave transforms from that layout and ends in the first one.  The C
+// lowest qubits are carried along, not transformed.
+template <int RB, int WB, bool CX, int C = 0, typename Real>
 __device__ __forceinline__ void fwd_wave(Cx<Real> (&v)[1 << RB], Cx<Real> *buf, uint32_t wave, uint32_t lane, uint32_t lam) {
+    static_assert(C == 0 || (WB != 0 && C <= 4), "carried qubits are lanes of a row");
     reg_layers<0, RB>(v);
     lane_layer<4, true, 0>(v, lam);
     lane_layer<5, true, 1>(v, lam);
     if constexpr (WB != 0) {
         wave_exchange<RB, WB, CX>(v, buf, wave, lane);
         reg_layers<RB - WB, RB>(v);
-        row_layers<0, 4, true>(v, lam);
+        row_layers<C, 4, true>(v, lam);
     } else {
         row_layers<2, 4, true>(v, lam);
         row_layers<0, 2, true>(v, lam);
     }
 }
 
-template <int RB, int WB, bool CX, typename Real>
+template <int RB, int WB, bool CX, int C = 0, typename Real>
 __device__ __forceinline__ void bwd_wave(Cx<Real> (&v)[1 << RB], Cx<Real> *buf, uint32_t wave, uint32_t lane, uint32_t lam) {
     // (with fewer than two register bits outside the exchange, lane bit 5 sits
     // in a wave bit until the exchange back)
     constexpr bool early5 = WB == 0 || RB - WB >= 2;
-    row_layers<0, 4, false>(v, lam);
+    row_layers<C, 4, false>(v, lam);
     lane_layer<4, false, 0>(v, lam);
     if constexpr (early5) lane_layer<5, false, 1>(v, lam);
     if constexpr (WB != 0) {
@@ -238,7 +240,7 @@ __device__ __forceinline__ void bwd_wave(Cx<Real> (&v)[1 << RB], Cx<Real> *buf, 
 
 // Index of register element q of a thread after fwd_wave.
 template <int RB, int WB>
-__device__ __forceinline__ uint32_t wave_index(uint32_t wave, uint32_t lam, uint32_t q) {
+__device__ __host__ constexpr uint32_t wave_index(uint32_t wave, uint32_t lam, uint32_t q) {
     constexpr int keep = RB - WB;
     const uint32_t w = WB ? q >> keep : 0u;                                   // wave bits, in the registers
     const uint32_t e = WB ? (wave << keep) | (q & ((1u << keep) - 1u)) : q;   // element before the exchange
@@ -246,6 +248,12 @@ __device__ __forceinline__ uint32_t wave_index(uint32_t wave, uint32_t lam, uint
     const uint32_t lo = (lam & 15u) | ((e & 1u) << 4) | ((e & 2u) << 4);
     const uint32_t el = (e & ~3u) | ((lam >> 4) & 3u);
     return lo | (w << 6) | (el << (6 + WB));
+}
+
+// Tile index bit of register bit r after fwd_wave (WB != 0).
+template <int RB, int WB>
+constexpr int wave_reg_bit(int r) {
+    return r >= RB - WB ? 6 + (r - (RB - WB)) : r < 2 ? 4 + r : 6 + WB + r;
 }
 
 }  // namespace z2h

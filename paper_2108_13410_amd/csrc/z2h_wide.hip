@@ -8,10 +8,9 @@
 // 2.5 TB/s).  Here the lane bits are transformed in the wave, and only the
 // three wave bits pass through LDS, once each way and one component at a
 // time (64 KiB), so two workgroups share a CU: 65 us, 4.1 TB/s (complex128:
-// step of a 13 + 11 qubit plan 373 -> 301 us).  What is left is the order of load, transform and
-// store within a workgroup; a copy in place of that size runs at 5.9 TB/s.
-// The layers run in the
-// general kernel's order (9-13, 4-8, 0-3 and back from the lowest window)
+// step of a 13 + 11 qubit plan 373 -> 301 us).  What is left is the order of
+// load, transform and store within a workgroup; a copy in place of that size
+// runs at 5.9 TB/s.  The layers run in the general kernel's order (9-13, 4-8, 0-3 and back from the lowest window)
 // and the norm's FP32 sums take its groups, so the bits are the same.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -25,12 +24,6 @@
 namespace z2h {
 
 namespace {
-
-// Index bit of register bit r after the forward layers (see wave_index).
-template <int RB, int WB>
-constexpr int wave_reg_bit(int r) {
-    return r >= RB - WB ? 6 + (r - (RB - WB)) : r < 2 ? 4 + r : 6 + WB + r;
-}
 
 // Sum of |v|^2 over the block, after the forward layers.  FP32 over the five
 // lowest index bits (pairwise from the highest, as the general pass sums a
