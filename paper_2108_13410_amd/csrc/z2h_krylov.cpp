@@ -31,9 +31,10 @@ int ham_workers(const GroupGeom &g) {
 
 // Groups of qubits a Hamiltonian pass is made for, and the workgroups (one
 // partial each) of the passes over a group.
-int ham_groups(const Plan &P) { return ham_wide_ok(P.c128, P.n) ? 2 : P.K; }
+bool ham_wave(const Plan &P) { return ham_wave_blocks(P.c128, P.n, false) > 0; }
+int ham_groups(const Plan &P) { return ham_wave(P) ? 2 : P.K; }
 int ham_workers(const Plan &P, int group) {
-    return ham_wide_ok(P.c128, P.n) ? kHamWideWorkers : ham_workers(P.geom[group]);
+    return ham_wave(P) ? ham_wave_blocks(P.c128, P.n, group > 0) : ham_workers(P.geom[group]);
 }
 
 unsigned vec_blocks(const Plan &P) {
@@ -49,7 +50,7 @@ static int ham_xcd(const Plan &P, int group, int workers) {
 
 // Pass i, over group gi.
 hipError_t launch_pass(const Plan &P, HamArgs &a, int gi, int i, hipStream_t s) {
-    if (ham_wide_ok(P.c128, P.n)) return launch_ham_wide(i < 2 ? i : !a.lz ? 3 : a.g ? 4 : 2, a, s);
+    if (ham_wave(P)) return launch_ham_wave(i < 2 ? i : !a.lz ? 3 : a.g ? 4 : 2, a, s);
     const int w = ham_workers(P, gi);
     a.geom = P.geom[gi];
     a.xcd = ham_xcd(P, gi, w);
@@ -154,7 +155,7 @@ bool coefs_inline(const Plan &P) { return ham_groups(P) > 1 && ham_workers(P, 0)
 // groups the update is fused into the Hamiltonian's passes (alpha from the
 // first and the top pass, w written by the last one); a one-group plan
 // forms y = H u and updates in an elementwise kernel.
-// acc (wide passes, k > 0): the Ritz vector takes u and p on the way.
+// acc (passes of two groups, k > 0): the Ritz vector takes u and p on the way.
 struct RitzAcc {
     void *g;
     double sp, su;
@@ -622,8 +623,8 @@ z2h_status z2h_lanczos_vector(const z2h_plan *plan, void *d_v, void *d_ws, size_
         void *u = d_v, *p = L.vec[0], *y = L.vec[1], *g = L.vec[2];
         // the same recurrence again (same kernels, so the same vectors),
         // accumulating g = sum_k s_k v_k, two vectors at a time; where the
-        // update's pass reads both anyway (wide passes), inside it
-        auto fused = [&](int k) { return ham_wide_ok(P.c128, P.n) && (k & 1) && k + 1 < iters; };
+        // update's pass reads both anyway, inside it
+        auto fused = [&](int k) { return ham_wave(P) && (k & 1) && k + 1 < iters; };
         if ((st = norm_start(P, u, L, s))) return st;
         const unsigned nb = vec_blocks(P);
         for (int k = 0; k < iters; ++k) {

@@ -277,91 +277,142 @@ __global__ void __launch_bounds__(512) ham_kernel(HamArgs a) {
     }
 }
 
-// Passes of y = H x over a 24-qubit complex128 state in two groups, the 13
-// low qubits and the 11 high ones: three passes where narrower groups take
-// five (ROLE 0 the low group forward, 1 the high group with the X-basis
-// diagonal, 2 and 3 the low group's way back with the Lanczos update or with
-// D_Z x added; 4 is 2 with the Ritz vector's sum of the two vectors it reads).  A tile of 2^13 elements is 128 KiB.  In ham_kernel it fills
-// the LDS: one workgroup per CU, four layout changes a pass, and three such
-// passes take as long as five of 2^12.  Here six bits are transformed in the
-// wave and the three wave bits through half of that LDS, one component at a
-// time, so two workgroups share a CU; the state between two passes stays in
-// the order the transform leaves it in (the same addresses), with the signs
-// that lane_layer defers.
+// Passes of y = H x over a complex128 state of N qubits in two groups, the
+// low and the high ones, three a product: ROLE 0 the low group forward, 1 the
+// high group with the X-basis diagonal, 2 and 3 the low group's way back with
+// the Lanczos update or with D_Z x added; 4 is 2 with the Ritz vector's sum of
+// the two vectors it reads.  Six bits are transformed in the wave, WB wave
+// bits through LDS once each way; the state between two passes stays in the
+// order the transform leaves it in (the same addresses), with the signs that
+// lane_layer defers.
 //
-// Two blocks per CU walk the tiles, so the coefficients are summed from 512
-// partials once for four tiles.  Tiles of the high group hold 64-byte runs;
-// neighbours meet in one XCD's L2.
+// 24 qubits: 13 + 11, where the plan's narrower groups take five passes.  A
+// tile of 2^13 elements is 128 KiB; in ham_kernel it fills the LDS (one
+// workgroup per CU, four layout changes a pass, and three such passes take as
+// long as five of 2^12).  Here one component at a time passes through half of
+// that LDS, so two workgroups share a CU and walk four tiles each, the
+// coefficients summed once from 512 partials.  Tiles of the high group hold
+// 64-byte runs; neighbours meet in one XCD's L2.  At 256 MiB a pass takes
+// 101 us (5.3 TB/s; a large copy 4.6, in place 5.9), 110 us (158 without the
+// row mixing below), 212 us for the update's four streams and 318 us for six;
+// a Lanczos iteration 649 -> 433 us, and 2 x 134 us less of separate
+// accumulation per two vectors for 106 us more here.  Two elements of each
+// operand at a time in the update: with four the registers spill (role 4:
+// 406 us).
 //
-// At 256 MiB a pass takes 101 us (5.3 TB/s; a large copy 4.6, in place 5.9),
-// 110 us (158 without the row mixing below), 212 us for the update's four
-// streams and 318 us for six; a Lanczos iteration 649 -> 433 us, and 2 x 134
-// us less of separate accumulation per two vectors for 106 us more here.
-// Two elements of each operand at a time in the update: with four the
-// registers spill (role 4: 406 us).
-template <int ROLE>
-__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) ham_wide_kernel(HamArgs a) {
+// 16 to 20 qubits: a pass is a chain of latencies (launch, tile, transform,
+// store), with few waves per CU.  Tiles are small (2^9 of one wave, without
+// any exchange, or 2^11 of four), and every operand is fetched at once before
+// the transform.  The three passes at 18 qubits, 3 x 10.4 us in ham_kernel:
+// 5.2 + 5.3 + 7.7 as 11 + 7 qubits, 5.0 + 8.1 + 6.9 as 9 + 9, 4.6 + 7.4 + 6.7
+// as 10 + 8 with four registers, 5.3 + 8.3 + 9.8 as 10 + 8 with sixteen.
+template <int N> struct HamShape {};
+template <> struct HamShape<16> { static constexpr int RB = 3, LOW = 0, HIGH = 0; };
+template <> struct HamShape<18> { static constexpr int RB = 3, LOW = 2, HIGH = 0; };
+template <> struct HamShape<20> { static constexpr int RB = 3, LOW = 2, HIGH = 2; };
+template <> struct HamShape<24> { static constexpr int RB = 4, LOW = 3, HIGH = 3; };
+
+// Of the passes over one group: wave bits, tile qubits, threads per block,
+// tiles per block (waves that share none of their tile), carried qubits.
+template <int N, bool high>
+struct HamTile {
+    using S = HamShape<N>;
+    static constexpr int RB = S::RB, WB = high ? S::HIGH : S::LOW, M = RB + 6 + WB, LOWQ = RB + 6 + S::LOW;
+    static constexpr int C = high ? M - (N - LOWQ) : 0, T = WB ? 64 << WB : 128, per = WB ? 1 : 2;
+    static constexpr bool wide = N == 24;
+    static constexpr uint32_t tiles = 1u << (N - M);
+    static constexpr uint32_t blocks = wide ? 512u : tiles / per;
+    static constexpr size_t buf = WB ? (wide ? sizeof(double) : sizeof(Cx<double>)) << M : 0;  // exchange
+};
+
+template <int ROLE, int N>
+__device__ __forceinline__ void ham_wave_body(const HamArgs &a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    constexpr int RB = 4, WB = 3, M = RB + 6 + WB, C = 2 * M - kHamWideQubits;
     constexpr bool high = ROLE == 1, lanczos = ROLE == 2 || ROLE == 4;
+    using G = HamTile<N, high>;
+    constexpr int RB = G::RB, WB = G::WB, M = G::M, C = G::C, LOWQ = G::LOWQ;
+    constexpr bool CX = G::wide;
+    constexpr uint32_t CH = G::wide ? 2 : 1u << RB;  // operand elements at a time
     using V = Cx<double>;
-    V *lds = reinterpret_cast<V *>(smem);  // one component of the tile
-    double *red = reinterpret_cast<double *>(smem + (sizeof(double) << M));
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, lam = wave_lane(lane);
+    V *lds = reinterpret_cast<V *>(smem);
+    double *red = reinterpret_cast<double *>(smem + G::buf);
+    const uint32_t lane = threadIdx.x & 63u, wave = WB ? threadIdx.x >> 6 : 0u, lam = wave_lane(lane);
     const V *src = reinterpret_cast<const V *>(a.src), *x = reinterpret_cast<const V *>(a.x);
     V *dst = reinterpret_cast<V *>(a.dst);
-    const uint32_t lb = xcd_major(blockIdx.x, gridDim.x);
+    const uint32_t lb = G::wide ? xcd_major(blockIdx.x, gridDim.x) : blockIdx.x;
     double acc = 0.0, sig = 0.0, alpha = 0.0, cp = 0.0;
-    if constexpr (lanczos) lanczos_coefs(a, red, sig, alpha, cp);
-    const double g0 = ROLE == 4 ? a.gs[0] * a.coef[a.k - 1].sigma : 0.0, g1 = a.gs[1] * sig;
+    if constexpr (lanczos && G::wide) lanczos_coefs(a, red, sig, alpha, cp);
     // Tile index of the thread's element q: nat(q) | nat_t as the transform
     // starts, fin(q) | fin_t as it ends; at() maps it to the state's (the
-    // high group's tile holds 2^C neighbours of each of its 2^11 elements).
-    // The q part of an address is uniform, the thread's byte offset fits 32
-    // bits.
+    // high group's tile holds 2^C neighbours of each of its elements).  The q
+    // part of an address is uniform, the thread's byte offset fits 32 bits.
     const uint32_t nat_t = (wave << 6) | lam, fin_t = wave_index<RB, WB>(wave, lam, 0u);
-    auto at = [](uint32_t i) -> uint32_t { return high ? (i & ((1u << C) - 1u)) | ((i >> C) << M) : i; };
+    auto at = [](uint32_t i) -> uint32_t { return high ? (i & ((1u << C) - 1u)) | ((i >> C) << LOWQ) : i; };
     auto nat = [&](uint32_t q) { return at(q << (6 + WB)); };
     auto fin = [&](uint32_t q) { return at(wave_index<RB, WB>(0u, 0u, q)); };
-    constexpr uint32_t row = (1u << M) - 1u, nat_q = row & ~((1u << (6 + WB - C + 3)) - 1u);
+    constexpr uint32_t low = (1u << C) - 1u, row = (1u << LOWQ) - 1u;
+    constexpr uint32_t nat_q = row & ~((1u << (6 + WB - C + 3)) - 1u);
     constexpr uint32_t fin_q = wave_index<RB, WB>(0u, 0u, (1u << RB) - 1u);
-    for (uint32_t tile = lb; tile < 1u << (kHamWideQubits - M); tile += gridDim.x) {
+    uint32_t tile = lb;
+    if constexpr (WB == 0) tile = lb * G::per + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    for (; tile < G::tiles; tile += gridDim.x * G::per) {
         const uint32_t t0 = high ? tile << C : tile << M;
         auto elem = [&](const V *b, uint32_t u, uint32_t off) -> const V & {
             return *reinterpret_cast<const V *>(reinterpret_cast<const char *>(b + u) + off);
         };
-        // Between the passes the element of the high index h and the low
-        // index l sits at l ^ (h << 3): the high group's rows, 128 KiB apart,
-        // then start in different memory channels.
-        auto mix = [](uint32_t h) { return (h << 3) & row; };
+        // 24 qubits: between the passes the element of the high index h and
+        // the low index l sits at l ^ (h << 3): the high group's rows,
+        // 128 KiB apart, then start in different memory channels.
+        auto mix = [](uint32_t h) -> uint32_t { return G::wide ? (h << 3) & row : 0u; };
         auto y_q = [&](uint32_t q) -> uint32_t {
             return high ? nat(q) | ((t0 ^ mix((q << (6 + WB)) >> C)) & nat_q) : t0 | (fin(q) ^ (mix(tile) & fin_q));
         };
-        const uint32_t y_t = high ? at(nat_t & ~((1u << C) - 1u)) | (((t0 ^ mix(nat_t >> C)) & (row & ~nat_q)) | (nat_t & ((1u << C) - 1u)))
-                                  : fin_t ^ (mix(tile) & ~fin_q);
+        const uint32_t y_t =
+            high ? at(nat_t & ~low) | (((t0 ^ mix(nat_t >> C)) & (row & ~nat_q)) | (nat_t & low)) : fin_t ^ (mix(tile) & ~fin_q);
         const uint32_t nat_b = nat_t * (uint32_t)sizeof(V), y_b = y_t * (uint32_t)sizeof(V);
         V v[1 << RB];
 #pragma unroll
         for (uint32_t q = 0; q < (1u << RB); ++q) v[q] = ROLE == 0 ? elem(src, t0 | nat(q), nat_b) : elem(src, y_q(q), y_b);
+
+        // operands of the update (g: read as x and taken zero times at first)
+        const V *p = reinterpret_cast<const V *>(a.use_prev ? a.p : a.x);  // (cp = 0 without one)
+        V *w = lanczos ? reinterpret_cast<V *>(a.w) : dst, *gout = reinterpret_cast<V *>(a.g);
+        const V *g = a.g_first ? x : gout;
+        const double gf = a.g_first ? 0.0 : 1.0;
+        V xv[CH], pv[CH], gv[CH];
+        auto fetch = [&](uint32_t c0, uint32_t off) {
+#pragma unroll
+            for (uint32_t i = 0; i < CH; ++i) {
+                const uint32_t q = (c0 + i) ^ ((c0 + i) >> 1);
+                if constexpr (ROLE >= 2) xv[i] = elem(x, t0 | nat(q), off);
+                if constexpr (lanczos) pv[i] = elem(p, t0 | nat(q), off);
+                if constexpr (ROLE == 4 && !G::wide) gv[i] = elem(g, t0 | nat(q), off);
+            }
+        };
+        if constexpr (!G::wide) fetch(0, nat_b);
+        if constexpr (lanczos && !G::wide) lanczos_coefs(a, red, sig, alpha, cp);
+        const double g0 = ROLE == 4 ? a.gs[0] * a.coef[a.k - 1].sigma : 0.0, g1 = ROLE == 4 ? a.gs[1] * sig : 0.0;
+
         LayCtx<RB> L;
         const uint32_t i0 = t0 | at(high ? fin_t : nat_t);
         L.w0 = popc(i0);
         if constexpr (high) {
             L.s0x = syndrome_direct(a.lat.xmask, i0);
 #pragma unroll
-            for (int r = 0; r < RB; ++r) L.lx[r] = a.lat.xsyn[wave_reg_bit<RB, WB>(r) - C + M];
-            fwd_wave<RB, WB, true, C>(v, lds, wave, lane, lam);
+            for (int r = 0; r < RB; ++r) L.lx[r] = a.lat.xsyn[wave_reg_bit<RB, WB>(r) - C + LOWQ];
+            fwd_wave<RB, WB, CX, C>(v, lds, wave, lane, lam);
             mul_diag_x<double, RB, 4>(v, L, a.lat, a.JA, a.hx, a.xscale, &acc);
-            bwd_wave<RB, WB, true, C>(v, lds, wave, lane, lam);
+            if constexpr (WB && !CX) __syncthreads();
+            bwd_wave<RB, WB, CX, C>(v, lds, wave, lane, lam);
         } else {
             L.s0z = syndrome_direct(a.lat.zmask, i0);
 #pragma unroll
             for (int r = 0; r < RB; ++r) L.lz[r] = a.lat.zsyn[6 + WB + r];
             if constexpr (ROLE == 0) {
                 if (a.part_z) acc += diag_norm_z<double, RB>(v, L, a.lat, a.JB, a.hz);
-                fwd_wave<RB, WB, true>(v, lds, wave, lane, lam);
+                fwd_wave<RB, WB, CX>(v, lds, wave, lane, lam);
             } else {
-                bwd_wave<RB, WB, true>(v, lds, wave, lane, lam);
+                bwd_wave<RB, WB, CX>(v, lds, wave, lane, lam);
             }
         }
         uint32_t ob = ROLE < 2 ? y_b : nat_b;
@@ -371,22 +422,10 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) h
             for (uint32_t q = 0; q < (1u << RB); ++q) const_cast<V &>(elem(dst, y_q(q), ob)) = v[q];
         } else {
             // + D_Z x, CH elements of each operand at a time
-            const V *p = reinterpret_cast<const V *>(a.use_prev ? a.p : a.x);  // (cp = 0 without one)
-            V *w = lanczos ? reinterpret_cast<V *>(a.w) : dst;
-            V *gout = reinterpret_cast<V *>(a.g);
-            const V *g = a.g_first ? x : gout;  // (gf = 0 then)
-            const double gf = a.g_first ? 0.0 : 1.0;
-            constexpr uint32_t CH = 2;
             uint32_t s = L.s0z;
 #pragma unroll
             for (uint32_t c0 = 0; c0 < (1u << RB); c0 += CH) {
-                V xv[CH], pv[CH];
-#pragma unroll
-                for (uint32_t i = 0; i < CH; ++i) {
-                    const uint32_t q = (c0 + i) ^ ((c0 + i) >> 1);
-                    xv[i] = elem(x, t0 | nat(q), ob);
-                    if constexpr (lanczos) pv[i] = elem(p, t0 | nat(q), ob);
-                }
+                if constexpr (G::wide) fetch(c0, ob);
 #pragma unroll
                 for (uint32_t i = 0; i < CH; ++i) {
                     const uint32_t idx = c0 + i, q = idx ^ (idx >> 1);
@@ -402,9 +441,10 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) h
                     const_cast<V &>(elem(w, t0 | nat(q), ob)) = r;
                 }
                 if constexpr (ROLE == 4) {
-                    V gv[CH];
+                    if constexpr (G::wide) {
 #pragma unroll
-                    for (uint32_t i = 0; i < CH; ++i) gv[i] = elem(g, t0 | nat((c0 + i) ^ ((c0 + i) >> 1)), ob);
+                        for (uint32_t i = 0; i < CH; ++i) gv[i] = elem(g, t0 | nat((c0 + i) ^ ((c0 + i) >> 1)), ob);
+                    }
 #pragma unroll
                     for (uint32_t i = 0; i < CH; ++i) {
                         const V o{gf * gv[i].x + g0 * pv[i].x, gf * gv[i].y + g0 * pv[i].y};
@@ -421,6 +461,16 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) h
         const double s = block_sum(acc, red);
         if (threadIdx.x == 0) part[lb] = s;
     }
+}
+
+template <int ROLE, int N>
+__global__ void __launch_bounds__((HamTile<N, (ROLE == 1)>::T)) ham_wave_kernel(HamArgs a) {
+    ham_wave_body<ROLE, N>(a);
+}
+// (two workgroups of 512 threads per CU)
+template <int ROLE>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) ham_wide_kernel(HamArgs a) {
+    ham_wave_body<ROLE, 24>(a);
 }
 
 // Deterministic sum of n partials by one block (every thread gets it).
@@ -605,26 +655,53 @@ hipError_t launch_ham(bool c128, int R, const HamArgs &a, unsigned workers, size
     return hipErrorInvalidValue;
 }
 
-bool ham_wide_ok(bool c128, int n) { return c128 && n == kHamWideQubits; }
+template <int N>
+static int wave_blocks(bool high) {
+    return (int)(high ? HamTile<N, true>::blocks : HamTile<N, false>::blocks);
+}
 
-template <int ROLE>
-static hipError_t do_ham_wide(const HamArgs &a, hipStream_t s) {
-    constexpr size_t lds = (sizeof(double) << 13) + 16 * sizeof(double);
-    const void *fn = reinterpret_cast<const void *>(&ham_wide_kernel<ROLE>);
-    hipError_t e = allow_lds(fn, lds);
+int ham_wave_blocks(bool c128, int n, bool high) {
+    if (!c128) return 0;
+    switch (n) {
+        case 16: return wave_blocks<16>(high);
+        case 18: return wave_blocks<18>(high);
+        case 20: return wave_blocks<20>(high);
+        case 24: return wave_blocks<24>(high);
+    }
+    return 0;
+}
+
+template <int ROLE, int N>
+static hipError_t do_ham_wave(const HamArgs &a, hipStream_t s) {
+    using G = HamTile<N, ROLE == 1>;
+    constexpr size_t lds = G::buf + 16 * sizeof(double);
+    void (*fn)(HamArgs) = nullptr;
+    if constexpr (G::wide) fn = ham_wide_kernel<ROLE>;
+    else fn = ham_wave_kernel<ROLE, N>;
+    hipError_t e = allow_lds(reinterpret_cast<const void *>(fn), lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(ham_wide_kernel<ROLE>, dim3(kHamWideWorkers), dim3(512), lds, s, a);
+    hipLaunchKernelGGL(fn, dim3(G::blocks), dim3(G::T), lds, s, a);
     return hipGetLastError();
 }
 
-hipError_t launch_ham_wide(int role, const HamArgs &a, hipStream_t s) {
-    if (!ham_wide_ok(true, a.lat.n)) return hipErrorInvalidValue;
+template <int N>
+static hipError_t do_ham_role(int role, const HamArgs &a, hipStream_t s) {
     switch (role) {
-        case 0: return do_ham_wide<0>(a, s);
-        case 1: return do_ham_wide<1>(a, s);
-        case 2: return do_ham_wide<2>(a, s);
-        case 3: return do_ham_wide<3>(a, s);
-        case 4: return do_ham_wide<4>(a, s);
+        case 0: return do_ham_wave<0, N>(a, s);
+        case 1: return do_ham_wave<1, N>(a, s);
+        case 2: return do_ham_wave<2, N>(a, s);
+        case 3: return do_ham_wave<3, N>(a, s);
+        case 4: return do_ham_wave<4, N>(a, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_ham_wave(int role, const HamArgs &a, hipStream_t s) {
+    switch (a.lat.n) {
+        case 16: return do_ham_role<16>(role, a, s);
+        case 18: return do_ham_role<18>(role, a, s);
+        case 20: return do_ham_role<20>(role, a, s);
+        case 24: return do_ham_role<24>(role, a, s);
     }
     return hipErrorInvalidValue;
 }

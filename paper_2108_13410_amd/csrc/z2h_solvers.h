@@ -47,7 +47,7 @@ struct HamArgs {
     int32_t record;            // 1: the last pass writes coef[k] (nothing follows that would)
     int32_t k, use_prev, lz;
     int32_t g_first;           // 1: g is written, not added to
-    void *g;                   // Ritz vector, or null: g += gs[0] sigma_{k-1} p + gs[1] sigma_k x (wide passes)
+    void *g;                   // Ritz vector, or null: g += gs[0] sigma_{k-1} p + gs[1] sigma_k x (passes of two groups)
     double gs[2];
     GroupGeom geom;
     LatticeDev lat;
@@ -118,15 +118,13 @@ struct DotArgs {
 
 constexpr int kVecBlocks = 2048;   // blocks of the elementwise Lanczos kernels
 constexpr int kHamWorkersMax = 2048;
-// Complex128 states of this size run the Hamiltonian in two groups of qubits
-// by kernels of their own, whatever the plan's groups (two tiles of 2^13
-// cover them with 64-byte runs); other sizes in the plan's.
-constexpr int kHamWideQubits = 24;
-constexpr int kHamWideWorkers = 512;   // two per CU
-
 hipError_t launch_ham(bool c128, int R, const HamArgs &a, unsigned workers, size_t lds, hipStream_t s);
-bool ham_wide_ok(bool c128, int n);
-hipError_t launch_ham_wide(int role, const HamArgs &a, hipStream_t s);   // (roles: see the kernel)
+// Complex128 states of 16, 18, 20 and 24 qubits (every lattice of several
+// passes below 28) run the Hamiltonian in two groups of qubits by kernels of
+// their own, whatever the plan's groups; others in the plan's.  Workgroups of
+// a pass over the low or the high group, or 0.
+int ham_wave_blocks(bool c128, int n, bool high);
+hipError_t launch_ham_wave(int role, const HamArgs &a, hipStream_t s);   // (roles: see the kernel)
 hipError_t launch_vec(bool c128, const VecArgs &a, unsigned blocks, hipStream_t s);
 hipError_t launch_scalar(const ScalarArgs &a, hipStream_t s);
 hipError_t launch_combine(bool c128, const CombineArgs &a, unsigned blocks, hipStream_t s);

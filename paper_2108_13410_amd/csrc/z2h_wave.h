@@ -208,7 +208,7 @@ __device__ __forceinline__ void wave_exchange(Cx<Real> (&v)[1 << RB], Cx<Real> *
 // lowest qubits are carried along, not transformed.
 template <int RB, int WB, bool CX, int C = 0, typename Real>
 __device__ __forceinline__ void fwd_wave(Cx<Real> (&v)[1 << RB], Cx<Real> *buf, uint32_t wave, uint32_t lane, uint32_t lam) {
-    static_assert(C == 0 || (WB != 0 && C <= 4), "carried qubits are lanes of a row");
+    static_assert(C <= 4, "carried qubits are lanes of a row");
     reg_layers<0, RB>(v);
     lane_layer<4, true, 0>(v, lam);
     lane_layer<5, true, 1>(v, lam);
@@ -217,23 +217,24 @@ __device__ __forceinline__ void fwd_wave(Cx<Real> (&v)[1 << RB], Cx<Real> *buf, 
         reg_layers<RB - WB, RB>(v);
         row_layers<C, 4, true>(v, lam);
     } else {
-        row_layers<2, 4, true>(v, lam);
-        row_layers<0, 2, true>(v, lam);
+        row_layers<(C < 2 ? 2 : C), 4, true>(v, lam);
+        row_layers<(C < 2 ? C : 2), 2, true>(v, lam);
     }
 }
 
 template <int RB, int WB, bool CX, int C = 0, typename Real>
 __device__ __forceinline__ void bwd_wave(Cx<Real> (&v)[1 << RB], Cx<Real> *buf, uint32_t wave, uint32_t lane, uint32_t lam) {
-    // (with fewer than two register bits outside the exchange, lane bit 5 sits
-    // in a wave bit until the exchange back)
-    constexpr bool early5 = WB == 0 || RB - WB >= 2;
+    // (the register bits that lane bits 4 and 5 trade places with may sit in
+    // wave bits until the exchange back)
+    constexpr bool early4 = WB == 0 || RB - WB >= 1, early5 = WB == 0 || RB - WB >= 2;
     row_layers<C, 4, false>(v, lam);
-    lane_layer<4, false, 0>(v, lam);
+    if constexpr (early4) lane_layer<4, false, 0>(v, lam);
     if constexpr (early5) lane_layer<5, false, 1>(v, lam);
     if constexpr (WB != 0) {
         reg_layers<RB - WB, RB>(v);
         wave_exchange<RB, WB, CX>(v, buf, wave, lane);
     }
+    if constexpr (!early4) lane_layer<4, false, 0>(v, lam);
     if constexpr (!early5) lane_layer<5, false, 1>(v, lam);
     reg_layers<0, RB>(v);
 }
@@ -250,10 +251,10 @@ __device__ __host__ constexpr uint32_t wave_index(uint32_t wave, uint32_t lam, u
     return lo | (w << 6) | (el << (6 + WB));
 }
 
-// Tile index bit of register bit r after fwd_wave (WB != 0).
+// Tile index bit of register bit r after fwd_wave.
 template <int RB, int WB>
 constexpr int wave_reg_bit(int r) {
-    return r >= RB - WB ? 6 + (r - (RB - WB)) : r < 2 ? 4 + r : 6 + WB + r;
+    return WB && r >= RB - WB ? 6 + (r - (RB - WB)) : r < 2 ? 4 + r : 6 + WB + r;
 }
 
 }  // namespace z2h

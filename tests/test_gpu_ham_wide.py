@@ -1,5 +1,5 @@
-"""The Hamiltonian's passes over a 24-qubit complex128 state (two groups of
-qubits whatever the plan's) through the Lanczos entry points: the recurrence's
+"""The Hamiltonian's passes over complex128 states of 16, 18, 20 and 24 qubits
+(two groups of qubits whatever the plan's) through the Lanczos entry points: the recurrence's
 coefficients against the recurrence written out with H x and inner products
 (H x itself is checked against the oracle's rows), the Ritz vector against the
 sum of those vectors, for even and odd iteration counts and plans with other
@@ -19,8 +19,9 @@ def start(n):
     return torch.randn(1 << n, dtype=torch.complex128, device="cuda", generator=g)
 
 
-@pytest.mark.parametrize("Lx,Ly,cfg,iters", [(3, 4, None, 2), (3, 4, "split=8:4:12:0/8:4:12:4/8:4:12:4", 5), (6, 2, None, 6)])
-def test_lanczos_24_qubits(Lx, Ly, cfg, iters):
+@pytest.mark.parametrize("Lx,Ly,cfg,iters", [(3, 4, None, 2), (3, 4, "split=8:4:12:0/8:4:12:4/8:4:12:4", 5), (6, 2, None, 6),
+                                             (2, 4, None, 1), (4, 2, None, 6), (3, 3, None, 7), (2, 5, None, 6), (5, 2, None, 3)])
+def test_lanczos_two_groups(Lx, Ly, cfg, iters):
     print(f"case lanczos {Lx}x{Ly} {cfg} iters={iters}", flush=True)
     plan = z2h.z2h_plan_create_config(Lx, Ly, z2h.Z2H_C128, cfg) if cfg else z2h.z2h_plan_create(Lx, Ly, z2h.Z2H_C128)
     H = (1.0, 0.8, 0.5, 0.3)
