@@ -49,7 +49,7 @@ SHIPPED_TABLE = os.path.join(ROOT, "paper_2108_13410_amd", "tuned_mi355x.txt")
 # keyed by their hash)
 EXACT_4X4_SPLIT = "split=12:4:12:0/10:4:13:3:h7@22/10:4:13:3,xcd=7"
 KERNEL_SRCS = [os.path.join(ROOT, "paper_2108_13410_amd", "csrc", f)
-               for f in ("z2h_kernels.hip", "z2h_tile.h", "z2h_kernels.h", "z2h_internal.h")]
+               for f in ("z2h_kernels.hip", "z2h_tile.h", "z2h_sched.h", "z2h_kernels.h", "z2h_internal.h")]
 
 
 def kernel_hash():
