@@ -183,6 +183,14 @@ __device__ __forceinline__ void lanczos_coefs(const HamArgs &a, double *red, dou
     }
 }
 
+// Two complex128 tiles of 16 elements are the register limit: the plaquette
+// masks are taken one at a time there.  All at once, held in scalar registers
+// through the tile loop, they spilled 10 vector registers: a 4x4 product took
+// 166.6 ms, a Lanczos iteration 181.5, now 157.8 and 170.4.  Other shapes have
+// room for all masks, which is 1% to 2% faster.
+template <typename Real, int R, bool PF>
+constexpr bool two_tile_limit = PF && sizeof(Real) == 8 && R == 4;
+
 // PF: the next tile's elements are loaded while the current one is
 // transformed (two register tiles; used where they fit without spilling).
 template <typename Real, int R, bool PF, bool SP>
@@ -203,6 +211,7 @@ __global__ void __launch_bounds__(512) ham_kernel(HamArgs a) {
     double sig = 0.0, alpha = 0.0, cp = 0.0;
     if (lz) lanczos_coefs(a, red, sig, alpha, cp);
 
+    constexpr bool kLoop = two_tile_limit<Real, R, PF>;
     const bool syn0 = a.final_pass || a.part_z;
     // logical block: first tile of the grid-stride walk and partial slot
     const uint32_t lb = a.xcd ? xcd_major(blockIdx.x, gridDim.x) : blockIdx.x;
@@ -211,7 +220,7 @@ __global__ void __launch_bounds__(512) ham_kernel(HamArgs a) {
     LayCtx<R> Ln;
     if constexpr (PF) {
         if (tile < tiles) {
-            lay_ctx<R, SP>(Ln, g, a.lat, tile, g.p[0], t, syn0, 0);
+            lay_ctx<R, SP, kLoop>(Ln, g, a.lat, tile, g.p[0], t, syn0, 0);
             load_tile<Real, R, false, SP>(vn, src, Ln);
         }
     }
@@ -224,7 +233,7 @@ __global__ void __launch_bounds__(512) ham_kernel(HamArgs a) {
             for (int q = 0; q < (1 << R); ++q) v[q] = vn[q];
             const uint64_t nt = tile + gridDim.x;
             if (nt < tiles) {
-                lay_ctx<R, SP>(Ln, g, a.lat, nt, g.p[0], t, syn0, 0);
+                lay_ctx<R, SP, kLoop>(Ln, g, a.lat, nt, g.p[0], t, syn0, 0);
                 load_tile<Real, R, false, SP>(vn, src, Ln);
             }
         } else {
@@ -625,14 +634,18 @@ static hipError_t do_ham_pf(const HamArgs &a, unsigned workers, size_t lds, hipS
 }
 
 // Two register tiles fit without spilling up to 256 bytes of elements per
-// thread, except complex64 at R = 5, whose 32 elements per tile need more
-// index and syndrome registers than the other shapes.
+// thread (complex128 at R = 4 to within two registers, its first syndromes
+// one mask at a time), except complex64 at R = 5, whose 32 elements per tile
+// need more index and syndrome registers than the other shapes.
 template <typename Real, int R>
 static hipError_t do_ham(const HamArgs &a, unsigned workers, size_t lds, hipStream_t s) {
     if (a.geom.m - R < 6 || a.geom.m - R > 9) return hipErrorInvalidConfiguration;  // launch bounds
     constexpr bool pf = (2 * sizeof(Real) << R) <= 256 && !(sizeof(Real) == 4 && R == 5);
     // groups in two runs of qubits take the kernel with their address map
     if (a.geom.hi) return do_ham_pf<Real, R, pf, true>(a, workers, lds, s);
+    // one tile a block (12 qubits): no next one to load, and all masks at once
+    if constexpr (two_tile_limit<Real, R, pf>)
+        if (1ull << a.geom.tiles_log2 <= workers) return do_ham_pf<Real, R, false, false>(a, workers, lds, s);
     return do_ham_pf<Real, R, pf, false>(a, workers, lds, s);
 }
 

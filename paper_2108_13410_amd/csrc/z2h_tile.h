@@ -178,9 +178,18 @@ __device__ __forceinline__ uint32_t syndrome_direct(const uint32_t *masks, uint6
     return s;
 }
 
-// want_syn: fill the syndromes; which: 0 plaquettes only, 1 stars only, 2
-// both (a phase pass needs only the basis it applies).
-template <int R, bool SPLIT = false>
+// The same over the lattice's own masks, one at a time: for kernels at their
+// register limit (all masks at once hold sixteen intermediates).
+__device__ __forceinline__ uint32_t syndrome_loop(const uint32_t *masks, int nst, uint64_t i) {
+    uint32_t s = 0;
+    const uint32_t ii = (uint32_t)i;
+    for (int k = 0; k < nst; ++k) s |= (uint32_t)(popc(ii & masks[k]) & 1) << k;
+    return s;
+}
+
+// want_syn: fill the syndromes (LOOP: by syndrome_loop); which: 0 plaquettes
+// only, 1 stars only, 2 both (a phase pass needs only the basis it applies).
+template <int R, bool SPLIT = false, bool LOOP = false>
 __device__ __forceinline__ void lay_ctx(LayCtx<R> &L, const GroupGeom &g, const LatticeDev &lat,
                                         uint64_t tile, int p, uint32_t t, bool want_syn, int which = 2) {
     L.i0 = glob<SPLIT>(g, tile, lay_base<R>(p, t));
@@ -195,8 +204,12 @@ __device__ __forceinline__ void lay_ctx(LayCtx<R> &L, const GroupGeom &g, const 
     }
     L.w0 = __builtin_popcountll(L.i0);
     if (want_syn) {
-        L.s0z = which != 1 ? syndrome_direct(lat.zmask, L.i0) : 0u;
-        L.s0x = which != 0 ? syndrome_direct(lat.xmask, L.i0) : 0u;
+        auto syndrome = [&](const uint32_t *masks) {
+            if constexpr (LOOP) return syndrome_loop(masks, lat.nst, L.i0);
+            else return syndrome_direct(masks, L.i0);
+        };
+        L.s0z = which != 1 ? syndrome(lat.zmask) : 0u;
+        L.s0x = which != 0 ? syndrome(lat.xmask) : 0u;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int b = SPLIT ? reg_bit(L, r) : L.gs + r;
