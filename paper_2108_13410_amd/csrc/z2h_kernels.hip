@@ -629,6 +629,10 @@ __device__ void build_diag_table(Cx<Real> *tab, int nst, int n, double dJ, doubl
     __syncthreads();
 }
 
+// Both states' elements are in registers at once, up to 246 of them a thread
+// (complex128, R = 4): one basis' syndromes only, and the phase's products as
+// the compiler contracts them (phase_mul's form spilled 16 registers there,
+// and at R = 3 took 140 instead of 124, three waves a SIMD instead of four).
 template <typename Real, int R, int NL>
 __global__ void __launch_bounds__(512) adj_kernel(AdjArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -645,8 +649,8 @@ __global__ void __launch_bounds__(512) adj_kernel(AdjArgs a) {
     Cx<Real> *A = reinterpret_cast<Cx<Real> *>(a.A);
     Cx<Real> *B = reinterpret_cast<Cx<Real> *>(a.B);
     LayCtx<R> L0, Lm;
-    lay_ctx<R, true>(L0, g, a.lat, tile, p0, t, true);
-    lay_ctx<R, true>(Lm, g, a.lat, tile, a.no_transform ? p0 : pl, t, true);
+    lay_ctx<R, true>(L0, g, a.lat, tile, p0, t, false);
+    lay_ctx<R, true>(Lm, g, a.lat, tile, a.no_transform ? p0 : pl, t, true, a.op.basis);
     Cx<Real> va[1 << R], vb[1 << R];
 
     if (a.mode == 0) {
@@ -666,7 +670,7 @@ __global__ void __launch_bounds__(512) adj_kernel(AdjArgs a) {
         build_diag_table<Real>(tab, nst, n, a.dJ, a.dh, a.dscale);
         load_tile<Real, R, false, true>(va, A, L0);
         if (!a.no_transform) fwd_full<Real, R, NL>(va, lds, x1, t);
-        apply_phase<Real, R>(va, Lm, a.op.basis, n, tab);
+        apply_phase<Real, R, 0, false>(va, Lm, a.op.basis, n, tab);
         if (!a.no_transform) bwd_full<Real, R, NL>(va, lds, x1, t);
         store_tile<Real, R, false, true>(va, B, L0);
         return;
@@ -686,8 +690,8 @@ __global__ void __launch_bounds__(512) adj_kernel(AdjArgs a) {
     }
     const double acc = block_sum(adj_reduce<Real, R>(va, vb, Lm, a.op.basis, nst, n, a.dJ, a.dh), red);
     if (t == 0 && a.part) a.part[tile] = acc;
-    apply_phase<Real, R>(va, Lm, a.op.basis, n, tab);
-    apply_phase<Real, R>(vb, Lm, a.op.basis, n, tab);
+    apply_phase<Real, R, 0, false>(va, Lm, a.op.basis, n, tab);
+    apply_phase<Real, R, 0, false>(vb, Lm, a.op.basis, n, tab);
     if (!a.no_transform) bwd_full<Real, R, NL>(va, lds, x1, t);
     store_tile<Real, R, false, true>(va, A, L0);
     if (!a.no_transform) bwd_full<Real, R, NL>(vb, lds, x1, t);

@@ -62,7 +62,9 @@ __device__ void build_table(Cx<Real> *tab, double2 *fac, int nst, int n, double 
 
 // Multiply every register element by T[k][w]: elements are visited in
 // Gray-code order so each step updates the syndrome by one uniform column.
-template <typename Real, int R, int PHASE_CHUNK = 0>
+// SPELLED: the product of phase_mul, so that kernels sharing a state round
+// alike; else the compiler contracts it as the registers allow.
+template <typename Real, int R, int PHASE_CHUNK = 0, bool SPELLED = true>
 __device__ __forceinline__ void apply_phase(Cx<Real> (&v)[1 << R], const LayCtx<R> &L, int basis,
                                             int n, const Cx<Real> *tab) {
     uint32_t s = basis ? L.s0x : L.s0z;
@@ -72,7 +74,8 @@ __device__ __forceinline__ void apply_phase(Cx<Real> (&v)[1 << R], const LayCtx<
     for (int idx = 0; idx < (1 << R); ++idx) {
         const int q = idx ^ (idx >> 1);
         if (idx) s ^= basis ? L.lx[__builtin_ctz(idx)] : L.lz[__builtin_ctz(idx)];
-        v[q] = phase_mul(v[q], tw[__umul24((uint32_t)popc(s), (uint32_t)W) + __builtin_popcount(q)]);
+        const Cx<Real> f = tw[__umul24((uint32_t)popc(s), (uint32_t)W) + __builtin_popcount(q)];
+        v[q] = SPELLED ? phase_mul(v[q], f) : cmul(v[q], f);
         // keep the table reads of at most eight elements in flight (register
         // pressure when a block holds two tiles)
         if (PHASE_CHUNK && (idx & (PHASE_CHUNK - 1)) == PHASE_CHUNK - 1) __builtin_amdgcn_sched_barrier(0);
