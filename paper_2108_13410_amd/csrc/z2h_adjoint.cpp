@@ -51,14 +51,19 @@ static z2h_status adj_launch(const Plan &P, AdjArgs &a, int group, hipStream_t s
 
 // A half block per state: groups in one run of qubits whose layout changes
 // exchange whole elements, with at most 256 threads a tile (two register
-// files of a larger one would not fit) and room for two tiles in LDS.
+// files of a larger one would not fit) and room for two tiles in LDS.  Up to
+// 24 qubits: there the latencies inside a pass count (3x3 complex128, 100
+// steps: 4.09 -> 3.45 ms; 24 qubits, 10 steps: 11.35 -> 10.64).  A state of 28
+// streams from HBM, and two workgroups per CU keep more loads in flight than
+// one that holds both states (3 steps: 86.5 ms, one state after the other
+// 79.2).
 static size_t pair_lds(const Plan &P, const GroupGeom &g) {
     return 2 * ((size_t)1 << (g.m - g.R * g.full)) * (size_t)g.lds_blk * P.esize +
            (((size_t)(P.nst + 1) * (P.n + 1) * P.esize + 31) & ~(size_t)15) + 16 * sizeof(double);
 }
 
 static bool pair_ok(const Plan &P) {
-    if (P.K < 2) return false;
+    if (P.K < 2 || P.n > 24) return false;
     for (int j = 0; j < P.K; ++j) {
         const GroupGeom &g = P.geom[j];
         if (!g.full || !g.lds_blk || g.cx || g.hi || g.m - g.R > 8 || pair_lds(P, g) > (size_t)kMaxLdsBytes) return false;
