@@ -34,33 +34,49 @@ namespace {
 
 // Shape of a state of RB + 6 + WB qubits: RB register bits, WB wave bits,
 // PW waves that only build tables (0: the stepping waves build them between
-// two chunks of phases).
-template <int RB_, int WB_, int PW_>
+// two chunks of phases), tables for at most CH phases at once.
+template <int RB_, int WB_, int PW_, int CH>
 struct Shape {
     static constexpr int RB = RB_, WB = WB_, PW = PW_;
     static constexpr int n = RB + 6 + WB, nst = n / 2, W = n + 1;
     static constexpr int entries = (nst + 1) * W, nfac = nst + 1 + W;
     static constexpr int step_waves = 1 << WB, waves = step_waves + PW;
     static constexpr int per_wave = 64 / nfac;                            // phases a wave builds at once
-    static constexpr int chunk = per_wave * (PW ? PW : step_waves);       // phases per chunk
+    static constexpr int chunk = CH;                                      // phases per chunk
+    static_assert(CH <= per_wave * (PW ? PW : step_waves) && (!PW || CH == per_wave * PW), "who builds a chunk");
     static constexpr int threads = 64 * waves;
     static constexpr int bufs = PW ? 2 : 1;
 };
-typedef Shape<2, 0, 3> Shape8;
-typedef Shape<4, 2, 0> Shape12;
+typedef Shape<2, 0, 3, 12> Shape8;
+typedef Shape<4, 2, 0, 12> Shape12;
+typedef Shape<4, 2, 0, 11> Shape12Two;  // two workgroups per CU
 
-template <typename S, typename Real>
+// EX: exchange regions (with one, a barrier more each way).
+template <typename S, typename Real, int EX>
 struct Lds {
     double2 tab[S::bufs][S::chunk][S::entries];
-    double2 fac[S::waves][64];
     double red[S::step_waves];
-    Cx<Real> ex[S::WB ? 2 : 1][S::WB ? (64 << (S::RB + S::WB)) : 1];
+    union {  // (stepping waves build tables between two steps, barriers on either side)
+        double2 fac[S::waves][64];
+        Cx<Real> ex[EX][S::WB ? (64 << (S::RB + S::WB)) : 1];
+    };
 };
+// Launches of more states than the GPU has CUs run two workgroups per CU: the
+// steps are chains of latencies, and a second chain fits between.  12 qubits,
+// complex64: 231 registers a thread, and 80 KiB of LDS with 11 tables.
+// Complex128: one exchange region (80 KiB), and 256 registers of the 346 that
+// a workgroup alone takes (75 spilled, nearly all used between two steps
+// only).  4096 ramps of 100 steps, one workgroup per CU against two: complex64
+// 6.93 and 4.36 ms, complex128 8.38 and 6.87; 320 ramps 0.90 and 0.62, 1.07
+// and 0.94; 256 ramps 0.49 and 0.50, 0.58 and 0.69.
+constexpr unsigned kCUs = 256;
+static_assert(2 * sizeof(Lds<Shape12Two, float, 2>) <= (size_t)kMaxLdsBytes &&
+                  2 * sizeof(Lds<Shape12Two, double, 1>) <= (size_t)kMaxLdsBytes, "two workgroups per CU");
 
-// Tables of phases p0 .. p0 + per_wave - 1 of the ramp (phase p is level
-// lev0 + p), by one wave, in FP64: T[k][w] = exp(i (alpha (nst - 2k) + beta
-// (n - 2w))), times 2^-n in the Hadamard basis.  The factors pass between
-// the wave's own lanes through LDS.
+// Tables of phases p0 .. p0 + per_wave - 1, those below nph, of the ramp
+// (phase p is level lev0 + p), by one wave, in FP64: T[k][w] = exp(i (alpha
+// (nst - 2k) + beta (n - 2w))), times 2^-n in the Hadamard basis.  The
+// factors pass between the wave's own lanes through LDS.
 template <typename S>
 __device__ __forceinline__ void build_phases(const JobDev &J, int lev0, int nph, int p0, double2 (*tab)[S::entries],
                                              double2 *fac, uint32_t lane) {
@@ -136,10 +152,11 @@ __device__ __forceinline__ double reg_norm(const Cx<Real> (&v)[N]) {
     return (double)a[0];
 }
 
-template <typename S, typename Real>
-__global__ void __launch_bounds__(S::threads) resident_kernel(ResidentArgs a) {
+template <typename S, typename Real, int EX>
+__global__ void __launch_bounds__(S::threads) __attribute__((amdgpu_waves_per_eu(S::WB && EX == 1 ? 2 : 1)))
+resident_kernel(ResidentArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    Lds<S, Real> &L = *reinterpret_cast<Lds<S, Real> *>(smem);
+    Lds<S, Real, EX> &L = *reinterpret_cast<Lds<S, Real, EX> *>(smem);
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, lam = wave_lane(lane);
     const JobDev J = job_record(a.jobs, (int)blockIdx.x, a.job_inline);
     if (J.steps <= 0) return;  // uniform
@@ -178,6 +195,7 @@ __global__ void __launch_bounds__(S::threads) resident_kernel(ResidentArgs a) {
             phase<Real, N>(v, atz, tab, 1.0);
             return;
         }
+        if constexpr (S::WB && EX == 1) __syncthreads();
         fwd_wave<S::RB, S::WB, false>(v, L.ex[0], wave, lane, lam);
         double f = 1.0;
         if (have_norm) {
@@ -190,7 +208,8 @@ __global__ void __launch_bounds__(S::threads) resident_kernel(ResidentArgs a) {
             if (J.renorm) f = 1.0 / sqrt(norm);
         }
         phase<Real, N>(v, atx, tab, f);
-        bwd_wave<S::RB, S::WB, false>(v, L.ex[S::WB ? 1 : 0], wave, lane, lam);
+        if constexpr (S::WB && EX == 1) __syncthreads();
+        bwd_wave<S::RB, S::WB, false>(v, L.ex[EX - 1], wave, lane, lam);
     };
 
     if constexpr (S::PW != 0) {
@@ -210,9 +229,9 @@ __global__ void __launch_bounds__(S::threads) resident_kernel(ResidentArgs a) {
     } else {
         for (int c = 0; c < nph; c += S::chunk) {
             __syncthreads();  // the last chunk's tables are no longer read
-            build_phases<S>(J, lev0, nph, c + (int)wave * S::per_wave, &L.tab[0][wave * S::per_wave], L.fac[wave], lane);
-            __syncthreads();
             const int hi = nph - c < S::chunk ? nph - c : S::chunk;
+            build_phases<S>(J, lev0, c + hi, c + (int)wave * S::per_wave, &L.tab[0][wave * S::per_wave], L.fac[wave], lane);
+            __syncthreads();
             for (int p = 0; p < hi; ++p) run(c + p, L.tab[0][p]);
         }
     }
@@ -222,31 +241,35 @@ __global__ void __launch_bounds__(S::threads) resident_kernel(ResidentArgs a) {
     }
 }
 
-template <typename S, typename Real>
+template <typename S, typename Real, int EX>
 hipError_t do_resident(const ResidentArgs &a, unsigned njobs, hipStream_t s) {
-    static_assert(sizeof(Lds<S, Real>) <= (size_t)kMaxLdsBytes, "LDS of one workgroup");
-    hipError_t e = set_lds(reinterpret_cast<const void *>(&resident_kernel<S, Real>), sizeof(Lds<S, Real>));
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((resident_kernel<S, Real>), dim3(njobs), dim3(S::threads), sizeof(Lds<S, Real>), s, a);
+    constexpr size_t lds = sizeof(Lds<S, Real, EX>);
+    static_assert(lds <= (size_t)kMaxLdsBytes, "LDS of one workgroup");
+    hipError_t e = set_lds(reinterpret_cast<const void *>(&resident_kernel<S, Real, EX>), lds);
+    if (e != hipSuccess || !njobs) return e;
+    hipLaunchKernelGGL((resident_kernel<S, Real, EX>), dim3(njobs), dim3(S::threads), lds, s, a);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t prepare_resident() {
-    hipError_t e = hipSuccess;
-    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void *>(&resident_kernel<Shape8, float>), sizeof(Lds<Shape8, float>));
-    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void *>(&resident_kernel<Shape8, double>), sizeof(Lds<Shape8, double>));
-    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void *>(&resident_kernel<Shape12, float>), sizeof(Lds<Shape12, float>));
-    if (e == hipSuccess) e = set_lds(reinterpret_cast<const void *>(&resident_kernel<Shape12, double>), sizeof(Lds<Shape12, double>));
-    return e;
+hipError_t launch_resident(bool c128, const ResidentArgs &a, unsigned njobs, hipStream_t s) {
+    if (a.lat.n == Shape8::n) return c128 ? do_resident<Shape8, double, 1>(a, njobs, s) : do_resident<Shape8, float, 1>(a, njobs, s);
+    if (a.lat.n != Shape12::n) return hipErrorInvalidValue;
+    if (njobs > kCUs) return c128 ? do_resident<Shape12Two, double, 1>(a, njobs, s) : do_resident<Shape12Two, float, 2>(a, njobs, s);
+    return c128 ? do_resident<Shape12, double, 2>(a, njobs, s) : do_resident<Shape12, float, 2>(a, njobs, s);
 }
 
-hipError_t launch_resident(bool c128, const ResidentArgs &a, unsigned njobs, hipStream_t s) {
-    if (a.lat.n == Shape8::n) return c128 ? do_resident<Shape8, double>(a, njobs, s) : do_resident<Shape8, float>(a, njobs, s);
-    if (a.lat.n == Shape12::n)
-        return c128 ? do_resident<Shape12, double>(a, njobs, s) : do_resident<Shape12, float>(a, njobs, s);
-    return hipErrorInvalidValue;
+// The dynamic-LDS limits only (no launch).
+hipError_t prepare_resident() {
+    ResidentArgs a{};
+    hipError_t e = do_resident<Shape8, float, 1>(a, 0, nullptr);
+    if (e == hipSuccess) e = do_resident<Shape8, double, 1>(a, 0, nullptr);
+    if (e == hipSuccess) e = do_resident<Shape12, float, 2>(a, 0, nullptr);
+    if (e == hipSuccess) e = do_resident<Shape12, double, 2>(a, 0, nullptr);
+    if (e == hipSuccess) e = do_resident<Shape12Two, float, 2>(a, 0, nullptr);
+    if (e == hipSuccess) e = do_resident<Shape12Two, double, 1>(a, 0, nullptr);
+    return e;
 }
 
 }  // namespace z2h

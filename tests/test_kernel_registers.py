@@ -73,3 +73,11 @@ def test_adjoint_in_registers(kernels, R, NL):
     k = kernels[f"adj_kernel<double, {R}, {NL}>"]
     assert k[".vgpr_spill_count"] == 0
     assert k[".vgpr_count"] <= (128 if R == 3 else 256)  # four waves a SIMD, two
+
+
+def test_one_workgroup_states_share_a_cu(kernels):
+    """12 qubits, four waves a workgroup: two workgroups a CU (their LDS is
+    checked where it is laid out)."""
+    for real, ex in (("float", 2), ("double", 1)):
+        k = kernels[f"resident_kernel<Shape<4, 2, 0, 11>, {real}, {ex}>"]
+        assert k[".vgpr_count"] + k.get(".agpr_count", 0) <= 256
