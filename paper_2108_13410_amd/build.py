@@ -20,7 +20,7 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
 
 SOURCES = ["z2h_kernels.hip", "z2h_resident.hip", "z2h_wide.hip", "z2h_host.cpp", "z2h_batch.cpp", "z2h_adjoint.cpp",
            "z2h_tune.cpp", "z2h_path.cpp",
-           "z2h_krylov_kernels.hip", "z2h_krylov.cpp", "z2h_gates.hip", "z2h_circuit.cpp",
+           "z2h_krylov_kernels.hip", "z2h_krylov.cpp", "z2h_gates.hip", "z2h_fine.hip", "z2h_circuit.cpp",
            "z2h_noalloc.cpp"]
 
 
@@ -42,7 +42,7 @@ def _compile(src, verbose):
 # others are host code only: the planner, launch sequences, batch and path
 # engines, exact-solver host routines and gate-list builders.
 DEVICE_SOURCES = ["z2h_kernels.hip", "z2h_resident.hip", "z2h_wide.hip", "z2h_krylov_kernels.hip", "z2h_gates.hip",
-                  "z2h_noalloc.cpp"]
+                  "z2h_fine.hip", "z2h_noalloc.cpp"]
 HOST_SOURCES = [s for s in SOURCES if s not in DEVICE_SOURCES]
 SANITIZE_DIR = os.path.join(BUILD, "sanitize")
 SANITIZED_LIB = os.path.join(SANITIZE_DIR, "libz2h.so")
