@@ -99,11 +99,13 @@ __global__ void __launch_bounds__(512) level_kernel(LevelArgs a) {
     }
     // norms are measured only where a renormalization or a trace uses them
     const bool need_norm = op.norm && (J.renorm || J.norm_trace);
+    // (the squares' form differs between the element types and loads; it is
+    // the one that earlier norms, and renormalized states, were rounded by)
     if (has_phase || need_norm) {
         LayCtx<R> Lm;
         lay_ctx<R, SP>(Lm, g, a.lat, tile, g.p[cur], t, has_phase, op.basis);
         if (need_norm) {
-            double s = block_sum(sumsq<Real, R>(v), red);
+            double s = block_sum(sumsq<Real, R, !(NT && sizeof(Real) == 4)>(v), red);
             if (t == 0 && J.norm_part) gst(J.norm_part, tile, s);
         }
         if (has_phase) apply_phase<Real, R>(v, Lm, op.basis, a.lat.n, tab);
@@ -367,7 +369,7 @@ __device__ __forceinline__ void pass_multi(const LevelArgs &a, const JobDev &J, 
             LayCtx<R> Ls;
             lay_ctx<R, CX != 0>(Ls, g, a.lat, tile0 + s, p0, t, true, op.basis);
             if (meas_norm) {
-                const double q = block_sum(sumsq<Real, R>(v[s]), red);
+                const double q = block_sum(sumsq<Real, R, false>(v[s]), red);
                 if (t == 0 && J.norm_part) gst(J.norm_part, tile0 + s, q);
             }
             apply_phase<Real, R, NT == 2 ? 8 : 0>(v[s], Ls, op.basis, n, tab);
@@ -396,7 +398,7 @@ __device__ __forceinline__ void pass_multi(const LevelArgs &a, const JobDev &J, 
         for (int s = 0; s < NT; ++s) {
             if constexpr (KIND == kPhaseB) {
                 if (meas_norm) {
-                    const double q = block_sum(sumsq<Real, R>(v[s]), red);
+                    const double q = block_sum(sumsq<Real, R, false>(v[s]), red);
                     if (t == 0 && J.norm_part) gst(J.norm_part, tile0 + s, q);
                 }
             }

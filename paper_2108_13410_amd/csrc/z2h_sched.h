@@ -84,12 +84,12 @@ __device__ __forceinline__ void apply_phase(Cx<Real> (&v)[1 << R], const LayCtx<
 
 // Sum of |v_q|^2 over a thread's register elements: pairwise in the storage
 // precision (complex64 steps accumulate in FP32), returned as FP64 for the
-// block and grid reductions.
-template <typename Real, int R>
+// block and grid reductions.  IM: the form of the squares (abs2).
+template <typename Real, int R, bool IM>
 __device__ __forceinline__ double sumsq(const Cx<Real> (&v)[1 << R]) {
     Real a[1 << R];
 #pragma unroll
-    for (int q = 0; q < (1 << R); ++q) a[q] = v[q].x * v[q].x + v[q].y * v[q].y;
+    for (int q = 0; q < (1 << R); ++q) a[q] = abs2<IM>(v[q]);
 #pragma unroll
     for (int h = (1 << R) >> 1; h > 0; h >>= 1) {
 #pragma unroll
