@@ -194,8 +194,12 @@ constexpr int kFineBits = 3;
 constexpr int kFineMinTile = 10;    // a wave's amplitudes
 // Largest state the fine pass takes.  Per Trotter step, before and now, tile
 // groups: 19 qubits complex128 648 -> 286 us, complex64 422 -> 243; 21 qubits
-// 902 -> 461 and 536 -> 382.  Its gain is the code a pass fetches and the
-// waves it has; a larger state runs enough tiles per block to amortize both.
+// 902 -> 461 and 536 -> 382.  A list of gadgets at 22 qubits: 641 -> 287 and
+// 235 -> 203 us, in register groups (the fine pass on groups of at most five
+// qubits) 551 -> 381 and 285 -> 264.  The line is where the pass was measured
+// to; it is not yet the crossing: at 25 qubits a fused step takes 14.05 ms
+// (complex128) and 4.17 (complex64) in the tile kernel, and with this line
+// moved 6.64 and 3.31, in register groups 13.7 and 4.92, moved 10.7 and 4.97.
 constexpr int kFineMaxQubits = 22;
 
 hipError_t launch_fine(bool c128, const FusedArgs &a, hipStream_t s);
