@@ -51,14 +51,14 @@ def test_more_states_than_cus(dtype, order):
 
 
 @pytest.mark.parametrize("order", [0, 1])
-@pytest.mark.parametrize("dtype", [z2h.Z2H_C64, z2h.Z2H_C128])
-def test_states_share_cus(dtype, order):
-    """4096 states against 256, one a CU: 14 times as long where every
-    further 256 wait for the ones before, 8.8 (complex64) and 11.9 where two
-    run side by side."""
+def test_states_share_cus(order):
+    """4096 complex64 states against 256, one a CU: 14 times as long where
+    every further 256 wait for the ones before, 9 where two run side by side
+    (complex128: 14 and 12, too near for a bound; its registers and LDS are
+    checked where they are laid out)."""
     t = []
     for count in (256, 4096):
-        b = Batch(count, dtype, order, 100)
+        b = Batch(count, z2h.Z2H_C64, order, 100)
         b.run()
         best = 1e9
         for _ in range(9):
@@ -66,5 +66,5 @@ def test_states_share_cus(dtype, order):
             b.run()
             best = min(best, time.perf_counter() - t0)
         t.append(best)
-        print(f"case resident share dtype={dtype} order={order} count={count}: {best * 1e6:.0f} us", flush=True)
-    assert t[1] < (11.5 if dtype == z2h.Z2H_C64 else 13.0) * t[0]
+        print(f"case resident share order={order} count={count}: {best * 1e6:.0f} us", flush=True)
+    assert t[1] < 11.5 * t[0]
